@@ -21,10 +21,12 @@
 #include "vmc_pipeline.hpp"
 
 using vmcx::AdjLayout;
-using vmcx::AoTiles;
 using vmcx::DenseLayout;
 using vmcx::MeasBufs;
 using vmcx::MeasBufsD;
+using vmcx::Prepared;
+using vmcx::ShellRec;
+using vmcx::ShellTiles;
 using vmcx::SweepLayout;
 using vmcx::EstArgs;
 using vmcx::SysDev;
@@ -65,12 +67,10 @@ struct vmc_ctx {
     std::vector<void *> allocs;
     double *d_C = nullptr, *d_R = nullptr, *d_Z = nullptr;
     vmcx::BasisDev bdev{};   // the determinant's basis tables
-    AoTiles tiles16{};       // its AO tiles: whole shells, <= 16 AOs
     // one- and three/four-body Jastrow (MJ = 0: absent): the Jastrow basis,
     // [xi3 | xi1] in column blocks of 64 ([nq][MJ][64], FP64 and FP32), xi1
     int MJ = 0, nq = 0;
     vmcx::BasisDev jdev{};
-    AoTiles jtiles16{}, jtiles32{};   // the Jastrow basis in tiles of <= 16 and <= 32 functions
     double *d_xiblk = nullptr, *d_xi1 = nullptr;
     // the Jastrow-parameter gradient's sums (jastrow_gradient): per launch
     // the FP64 basis values at the electrons and the partial sums, and the
@@ -111,9 +111,13 @@ struct vmc_ctx {
     void *Kst = nullptr;     // [max_walkers][2][KN][KN] persistent inverses (type T)
     uint8_t *Ksig = nullptr; // [max_walkers][2][KN]
     int *Kstale = nullptr;   // [max_walkers][2]
-    float *d_Cf = nullptr;   // C in FP32 (mixed precision)
-    float *d_Cm = nullptr;   // FP32 copy of a caller's C (mixed precision)
-    double *d_cpad = nullptr;   // C padded for the MO-row kernel ((M + 16) x 64, either type)
+    // C and the nuclei as the kernels read them: the context's own (prepared
+    // once) and a caller's (prepared on its stream by each call that takes C
+    // and R); the records of all tilings (mo, j16, j32 one after another)
+    // without positions are their common source
+    Prepared own, user;
+    std::vector<ShellRec> h_rec;
+    ShellRec *d_rec = nullptr;
     // FP64 re-measurement of the walkers whose E_L is most sensitive to the
     // FP32 orbital values (mixed precision)
     AdjLayout al64{};
@@ -311,17 +315,23 @@ struct KStateRef {
 };
 
 template <typename T>
-static int measure_core(vmc_ctx *c, const double *pos, const double *pos0, int64_t cw, const T *C, const double *R,
+static int measure_core(vmc_ctx *c, const double *pos, const double *pos0, int64_t cw, const Prepared &P,
                         const double *R0, int warp, int full, const WalkerOut &o, const AdjLayout &al, double *pkey,
                         bool prof, const KStateRef &ks, hipStream_t st) {
     const SysDev &S = c->sys;
+    const double *R = P.R;
+    const T *C;
+    if constexpr (sizeof(T) == sizeof(float))
+        C = P.Cf;
+    else
+        C = P.C;
     T *phi = (T *)c->mb_phi;
     MeasBufs<T> mb{pos,         pos0,       phi,       (full || c->has_ecp) ? (T *)c->mb_ktil : nullptr,
                    (T *)c->mb_abar, c->mb_gb,   c->mb_dpart, c->mb_tao,
                    pkey,      (const T *)ks.K,                  ks.sig,
                    ks.stale};
     int pi = prof_begin(c, VMC_K_MO_ROWS, prof, cw, st);
-    HIP_OK(c, vmcx::launch_mo_rows_mfma<T>(S, C, R, pos, cw * c->N, c->tiles16, phi, 5, (T *)c->d_cpad, st));
+    HIP_OK(c, vmcx::launch_mo_rows_mfma<T>(S, P, pos, cw * c->N, phi, 5, st));
     prof_end(c, VMC_K_MO_ROWS, pi, st);
     // pseudopotential: the pairs inside the cutoffs, their points and the
     // MO rows there (values; with the adjoint also gradients)
@@ -332,8 +342,8 @@ static int measure_core(vmc_ctx *c, const double *pos, const double *pos0, int64
         pi = prof_begin(c, VMC_K_ECP_POINTS, prof, cw, st);
         HIP_OK(c, vmcx::launch_ecp_pairs(S, c->edev, R, pos, (int)cw, c->ecp_id0, c->ecp_idlist, c->ecp_rot,
                                          c->e_pairs, c->e_npairs, c->e_off, c->e_nrows, c->e_qpos, c->status, st));
-        HIP_OK(c, vmcx::launch_mo_rows_mfma<T>(S, C, R, c->e_qpos, cw * c->edev.pcap * 12, c->tiles16,
-                                               (T *)c->e_phiq, enc, (T *)c->d_cpad, st, c->e_nrows));
+        HIP_OK(c, vmcx::launch_mo_rows_mfma<T>(S, P, c->e_qpos, cw * c->edev.pcap * 12, (T *)c->e_phiq, enc, st,
+                                               c->e_nrows));
         prof_end(c, VMC_K_ECP_POINTS, pi, st);
     }
     const int64_t jrows = cw * c->N;
@@ -342,7 +352,7 @@ static int measure_core(vmc_ctx *c, const double *pos, const double *pos0, int64
         // one-/three-body Jastrow: chi with its gradients and Laplacians, the
         // value products with [xi3 | xi1]; gradient, Laplacian and value per
         // walker (the dense kernel adds them)
-        HIP_OK(c, vmcx::launch_jas_values<T>(c->jdev, c->jtiles16, R, pos, jrows, jX, st, jD, &c->jtiles32));
+        HIP_OK(c, vmcx::launch_jas_values<T>(c->MJ, P, pos, jrows, jX, st, jD));
         const int pg = prof_begin(c, VMC_K_JAS_GEMM, prof, cw, st);
         HIP_OK(c, vmcx::launch_jas_vprod<T>(c->MJ, c->nq, jrows, jX, (const T *)nullptr, xi_blocks<T>(c), jV, st));
         prof_end(c, VMC_K_JAS_GEMM, pg, st);
@@ -402,14 +412,13 @@ static int measure_core(vmc_ctx *c, const double *pos, const double *pos0, int64
 }
 
 // One measurement of `cw` walkers at positions pos0 (device [cw][N][3]) with
-// the caller's FP64 C: forward always; adjoint when `full`.  Outputs already
-// offset to the chunk.  In mixed precision C is rounded to FP32, and the
-// walkers the dense kernel flags as sensitive are measured again in
-// FP64 (gathered, measured, scattered over their mixed results).
-static int run_measure(vmc_ctx *c, const double *pos0, int64_t cw, const double *C, const double *R,
-                       const double *R0, int warp, int full, const WalkerOut &o, hipStream_t st,
-                       const KStateRef &ks = KStateRef()) {
+// the C and nuclei of P: forward always; adjoint when `full`.  Outputs already
+// offset to the chunk.  In mixed precision the walkers the dense kernel flags
+// as sensitive are measured again in FP64 (gathered, measured, scattered over their mixed results).
+static int run_measure(vmc_ctx *c, const double *pos0, int64_t cw, const Prepared &P, const double *R0, int warp,
+                       int full, const WalkerOut &o, hipStream_t st, const KStateRef &ks = KStateRef()) {
     const SysDev &S = c->sys;
+    const double *R = P.R;
     const double *pos = pos0;
     if (warp) {
         HIP_OK(c, vmcx::launch_warp(S, R, R0, pos0, c->mb_posw, o.lnjac ? o.lnjac : c->st_lnjac, (int)cw, st));
@@ -418,19 +427,14 @@ static int run_measure(vmc_ctx *c, const double *pos0, int64_t cw, const double 
         HIP_OK(c, hipMemsetAsync(o.lnjac, 0, cw * sizeof(double), st));
     }
     if (c->opt.precision != VMC_MIXED)
-        return measure_core<double>(c, pos, pos0, cw, C, R, R0, warp, full, o, c->al, nullptr, true, ks, st);
-    const float *Cf = c->d_Cf;
-    if (C != c->d_C) {
-        HIP_OK(c, vmcx::launch_round_f32(C, c->d_Cm, (int64_t)c->M * c->n_occ, st));
-        Cf = c->d_Cm;
-    }
+        return measure_core<double>(c, pos, pos0, cw, P, R0, warp, full, o, c->al, nullptr, true, ks, st);
     // the walkers re-measured in FP64: a fixed share of the launch, those
     // with the largest max|Abar| (known count: no host round trip)
     const int64_t cnt = c->opt.promote_fraction > 0.0
                             ? std::min<int64_t>(cw, (int64_t)std::ceil(c->opt.promote_fraction * (double)cw))
                             : 0;
-    int rc = measure_core<float>(c, pos, pos0, cw, Cf, R, R0, warp, full, o, c->al, cnt ? c->pkey : nullptr, true,
-                                 ks, st);
+    int rc = measure_core<float>(c, pos, pos0, cw, P, R0, warp, full, o, c->al, cnt ? c->pkey : nullptr, true, ks,
+                                 st);
     if (rc || !cnt) return rc;
     HIP_OK(c, vmcx::launch_promote_select(c->pkey, (int)cw, (int)cnt, c->plist, st));
     const int64_t N3 = 3 * (int64_t)c->N, A3 = 3 * (int64_t)c->A, Mn = (int64_t)c->M * c->n_occ;
@@ -444,7 +448,7 @@ static int run_measure(vmc_ctx *c, const double *pos0, int64_t cw, const double 
                      o.dlnjac_dR ? c->cp_dJdR : nullptr, (o.O || o.Of) ? c->cp_O : nullptr,
                      (o.G || o.Gf) ? c->cp_G : nullptr};
         c->ecp_idlist = lst;
-        rc = measure_core<double>(c, c->cp_pos, c->cp_pos0, kc, C, R, R0, warp, full, oc, c->al64, nullptr, false,
+        rc = measure_core<double>(c, c->cp_pos, c->cp_pos0, kc, P, R0, warp, full, oc, c->al64, nullptr, false,
                                   KStateRef(), st);
         c->ecp_idlist = nullptr;
         if (rc) return rc;
@@ -466,18 +470,17 @@ static int run_measure(vmc_ctx *c, const double *pos0, int64_t cw, const double 
 // (and Jastrow terms) -- independent of the moves' outcomes -- then the moves.
 template <typename T>
 static int sweep_once(vmc_ctx *c, double *walkers, int64_t W, int t, uint32_t sidx, uint64_t seed, uint8_t *acc_t,
-                      const T *C, hipStream_t st) {
+                      hipStream_t st) {
     const int64_t rows = W * c->N;
     T *Amo = (T *)c->Amo;
     const int pp = prof_begin(c, VMC_K_PROPOSALS, true, W, st);
     HIP_OK(c, vmcx::launch_propose(walkers, W, c->N, sidx, seed, c->opt.step_sigma, c->prop, st));
-    HIP_OK(c, vmcx::launch_mo_rows_mfma<T>(c->sys, C, c->d_R, c->prop, rows, c->tiles16, (T *)c->Phip, 1,
-                                          (T *)c->d_cpad, st));
+    HIP_OK(c, vmcx::launch_mo_rows_mfma<T>(c->sys, c->own, c->prop, rows, (T *)c->Phip, 1, st));
     vmcx::JasSweep<T> js;
     if (c->MJ > 0) {
         T *Xp = (T *)c->js_Xp, *X0 = (T *)c->js_X0, *Pd = (T *)c->js_Pd;
-        HIP_OK(c, vmcx::launch_jas_values<T>(c->jdev, c->jtiles16, c->d_R, c->prop, rows, Xp, st));
-        HIP_OK(c, vmcx::launch_jas_values<T>(c->jdev, c->jtiles16, c->d_R, walkers, rows, X0, st));
+        HIP_OK(c, vmcx::launch_jas_values<T>(c->MJ, c->own, c->prop, rows, Xp, st));
+        HIP_OK(c, vmcx::launch_jas_values<T>(c->MJ, c->own, walkers, rows, X0, st));
         const int pg = prof_begin(c, VMC_K_JAS_GEMM, true, W, st);
         HIP_OK(c, vmcx::launch_jas_vprod<T>(c->MJ, c->nq, rows, Xp, X0, xi_blocks<T>(c), Pd, st));
         prof_end(c, VMC_K_JAS_GEMM, pg, st);
@@ -492,8 +495,7 @@ static int sweep_once(vmc_ctx *c, double *walkers, int64_t W, int t, uint32_t si
     // the MO matrix of every walker from the caller's positions; the sweeps
     // keep it current (row e rewritten on each accepted move)
     if (t == 0)
-        HIP_OK(c, vmcx::launch_mo_rows_mfma<T>(c->sys, C, c->d_R, walkers, rows, c->tiles16, Amo, 1, (T *)c->d_cpad,
-                                              st));
+        HIP_OK(c, vmcx::launch_mo_rows_mfma<T>(c->sys, c->own, walkers, rows, Amo, 1, st));
     const int pi = prof_begin(c, VMC_K_SWEEP, true, W, st);
     const vmcx::KState<T> ks{(T *)c->Kst, c->Ksig, c->Kstale};
     HIP_OK(c, vmcx::launch_sweep<T>(c->sys, (const T *)c->Phip, c->prop, walkers, (int)W, Amo, ks, t == 0, sidx, seed,
@@ -537,7 +539,7 @@ static int measure_accumulate(vmc_ctx *c, const double *walkers, int64_t W, cons
             ks.stale = c->Kstale + 2 * c0;
         }
         c->ecp_id0 = c0;
-        if ((rc = run_measure(c, walkers + c0 * c->N * 3, cw, c->d_C, c->d_R, c->d_R, 0, 1, o, st, ks))) return rc;
+        if ((rc = run_measure(c, walkers + c0 * c->N * 3, cw, c->own, c->d_R, 0, 1, o, st, ks))) return rc;
         HIP_OK(c, vmcx::launch_set_shift(c->st_EL, cw, c->shift, c->shift_set, st));
         EstArgs a{c->st_EL, c->st_dEdR, c->st_dPdR, c->st_dJdR, c->st_O, c->st_G, c->shift,
                   nullptr,  nullptr,    nullptr,    A3,         Mn};
@@ -549,8 +551,7 @@ static int measure_accumulate(vmc_ctx *c, const double *walkers, int64_t W, cons
         if (c->xg_n > 0) {
             // the Jastrow-parameter sums of this launch (basis values again in
             // FP64: the measurement's may have been replaced by a promoted subset)
-            HIP_OK(c, vmcx::launch_jas_values<double>(c->jdev, c->jtiles16, c->d_R, walkers + c0 * c->N * 3,
-                                                      cw * c->N, c->xg_X, st));
+            HIP_OK(c, vmcx::launch_jas_values<double>(c->MJ, c->own, walkers + c0 * c->N * 3, cw * c->N, c->xg_X, st));
             HIP_OK(c, vmcx::launch_xi_sums(c->xg_X, c->N, c->MJ, (int)cw, c->st_EL, c->shift, a.wt, c->xg_part,
                                            c->xg_scr, c->xg_acc, c->xg_comp, st));
         }
@@ -599,10 +600,11 @@ static size_t ts_of(int precision) { return precision == VMC_MIXED ? sizeof(floa
 
 // Fold the GTO normalisation of a basis (coefficients of unit-normalised
 // primitives; every cartesian component renormalised to unit norm) and upload
-// its tables and AO tiles (whole shells of at most 16 AOs).  Shell counts,
-// angular momenta and exponents have been validated.
-static int upload_basis(vmc_ctx *c, const vmc_basis *basis, int A, vmcx::BasisDev &bd, AoTiles &tiles,
-                        AoTiles *tiles32 = nullptr) {
+// its tables and AO tiles (whole shells of at most 16 AOs; with tiles32 also
+// of at most 32), the shells' records appended to the context's.  Shell
+// counts, angular momenta and exponents have been validated.
+static int upload_basis(vmc_ctx *c, const vmc_basis *basis, int A, vmcx::BasisDev &bd, ShellTiles &tiles,
+                        ShellTiles *tiles32 = nullptr) {
     const int S = basis->n_shells;
     int P = 0;
     for (int s = 0; s < S; ++s) P += basis->shell_nprim[s];
@@ -640,30 +642,54 @@ static int upload_basis(vmc_ctx *c, const vmc_basis *basis, int A, vmcx::BasisDe
         }
     }
     const int M = (int)ao_shell.size();
-    // AO tiles: consecutive whole shells with at most mt AOs, as four arrays
-    // (first shell, end shell, first AO, end AO)
+    // AO tiles: consecutive whole shells with at most mt AOs; a tile's shells
+    // are dealt to the four wavefronts of a row block by decreasing cost (in
+    // VALU instructions, about), each to the least loaded one, so that the
+    // block's barrier waits for the least: with one d shell per tile in the
+    // shells' own order, one wavefront had 1.7 times the average
     auto make_tiles = [&](int mt) {
-        std::vector<int> tl;
+        std::vector<vmcx::TileHdr> hdr;
         for (int s = 0; s < S;) {
             int s1 = s, cnt = 0;
-            while (s1 < S && cnt + (basis->shell_l[s1] + 1) * (basis->shell_l[s1] + 2) / 2 <= mt) {
-                cnt += (basis->shell_l[s1] + 1) * (basis->shell_l[s1] + 2) / 2;
-                ++s1;
+            while (s1 < S && cnt + vmcx::n_cart(basis->shell_l[s1]) <= mt) cnt += vmcx::n_cart(basis->shell_l[s1++]);
+            auto cost = [&](int q) { return 20 + 10 * basis->shell_nprim[q] + 18 * vmcx::n_cart(basis->shell_l[q]); };
+            std::vector<int> ord;
+            for (int q = s; q < s1; ++q) ord.push_back(q);
+            std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) { return cost(a) > cost(b); });
+            std::vector<int> of[4];
+            int load[4] = {0, 0, 0, 0};
+            for (int q : ord) {
+                const int v = (int)(std::min_element(load, load + 4) - load);
+                of[v].push_back(q);
+                load[v] += cost(q);
             }
-            tl.push_back(s);
-            tl.push_back(s1);
-            tl.push_back(shell_mu0[s]);
-            tl.push_back(s1 < S ? shell_mu0[s1] : M);
+            vmcx::TileHdr h{shell_mu0[s], cnt, (int)c->h_rec.size(), 0};
+            unsigned end = 0, packed = 0;
+            for (int v = 0; v < 4; ++v) {
+                end += (unsigned)of[v].size();
+                packed |= end << (8 * v);
+                for (int q : of[v]) {
+                    ShellRec r{};
+                    const int np = basis->shell_nprim[q];
+                    for (int k = 0; k < std::min(np, vmcx::REC_PRIM); ++k) {
+                        r.al[k] = basis->prim_exp[shell_p0[q] + k];
+                        r.cp[k] = cp[shell_p0[q] + k];
+                        r.alf[k] = (double)(float)r.al[k];
+                        r.cpf[k] = (float)r.cp[k];
+                    }
+                    r.lnp = basis->shell_l[q] | np << 8;
+                    r.p0 = shell_p0[q];
+                    r.dmu = shell_mu0[q] - shell_mu0[s];
+                    r.atom = basis->shell_atom[q];
+                    c->h_rec.push_back(r);
+                }
+            }
+            h.w = (int)packed;
+            hdr.push_back(h);
             s = s1;
         }
-        const int n = (int)tl.size() / 4;
-        std::vector<int> soa(4 * n);
-        for (int t = 0; t < n; ++t)
-            for (int k = 0; k < 4; ++k) soa[k * n + t] = tl[4 * t + k];
-        return soa;
+        return hdr;
     };
-    const std::vector<int> soa = make_tiles(16);
-    const int nt = (int)soa.size() / 4;
     // the AOs of each atom (any shell order), for per-nucleus sums
     std::vector<int> atom_ao_ptr(A + 1, 0), atom_ao(M);
     for (int m = 0; m < M; ++m) ++atom_ao_ptr[basis->shell_atom[ao_shell[m]] + 1];
@@ -672,12 +698,11 @@ static int upload_basis(vmc_ctx *c, const vmc_basis *basis, int A, vmcx::BasisDe
         std::vector<int> fill(atom_ao_ptr.begin(), atom_ao_ptr.end() - 1);
         for (int m = 0; m < M; ++m) atom_ao[fill[basis->shell_atom[ao_shell[m]]]++] = m;
     }
-    int *d_ao_shell, *d_ao_pow, *d_shell_atom, *d_shell_p0, *d_shell_np, *d_shell_l, *d_shell_mu0, *d_ptr, *d_aa,
-        *d_tiles;
+    int *d_ao_shell, *d_ao_pow, *d_shell_atom, *d_shell_p0, *d_shell_np, *d_shell_l, *d_shell_mu0, *d_ptr, *d_aa;
     double *d_eta, *d_exp, *d_cp;
     int rc;
     if ((rc = c->upload(&d_shell_l, (const int *)basis->shell_l, S)) ||
-        (rc = c->upload(&d_shell_mu0, shell_mu0.data(), S)) || (rc = c->upload(&d_tiles, soa.data(), 4 * nt)) ||
+        (rc = c->upload(&d_shell_mu0, shell_mu0.data(), S)) ||
         (rc = c->upload(&d_ptr, atom_ao_ptr.data(), A + 1)) || (rc = c->upload(&d_aa, atom_ao.data(), M)) ||
         (rc = c->upload(&d_ao_shell, ao_shell.data(), M)) || (rc = c->upload(&d_ao_pow, ao_pow.data(), M)) ||
         (rc = c->upload(&d_eta, ao_eta.data(), M)) ||
@@ -688,14 +713,42 @@ static int upload_basis(vmc_ctx *c, const vmc_basis *basis, int A, vmcx::BasisDe
         return rc;
     bd = vmcx::BasisDev{M,           S,         d_ao_shell, d_ao_pow, d_eta,       d_shell_atom, d_shell_p0,
                         d_shell_np, d_exp,     d_cp,       d_shell_l, d_shell_mu0, d_ptr,        d_aa};
-    tiles = AoTiles{d_tiles, d_tiles + nt, d_tiles + 2 * nt, d_tiles + 3 * nt, nt};
-    if (tiles32) {
-        const std::vector<int> s32 = make_tiles(32);
-        const int n32 = (int)s32.size() / 4;
-        int *d32;
-        if ((rc = c->upload(&d32, s32.data(), 4 * n32))) return rc;
-        *tiles32 = AoTiles{d32, d32 + n32, d32 + 2 * n32, d32 + 3 * n32, n32};
-    }
+    auto tiling = [&](int mt, ShellTiles &t) {
+        const std::vector<vmcx::TileHdr> hdr = make_tiles(mt);
+        vmcx::TileHdr *d_hdr;
+        const int rc = c->upload(&d_hdr, hdr.data(), hdr.size());
+        // (the records' base is set when they are all known)
+        if (!rc) t = ShellTiles{d_hdr, nullptr, (int)hdr.size(), d_exp, d_cp};
+        return rc;
+    };
+    if ((rc = tiling(16, tiles))) return rc;
+    return tiles32 ? tiling(32, *tiles32) : VMC_OK;
+}
+
+// P's copies of C and the shells' records at the nuclei R (device), queued on
+// st; P keeps pointing at the caller's C and R for the kernels of this call.
+static int prepare(vmc_ctx *c, Prepared &P, const double *C, const double *R, hipStream_t st) {
+    P.C = C;
+    P.R = R;
+    HIP_OK(c, vmcx::launch_prepare(C, c->M, c->n_occ, R, c->d_rec, (int)c->h_rec.size(), (double *)P.Cp,
+                                   (float *)P.Cpf, (float *)P.Cf, (ShellRec *)P.mo.rec, st));
+    return VMC_OK;
+}
+
+// The buffers of a Prepared, sharing t's tile headers.
+static int alloc_prepared(vmc_ctx *c, Prepared &P, bool mixed) {
+    double *Cp = nullptr;
+    float *Cpf = nullptr, *Cf = nullptr;
+    ShellRec *rec = nullptr;
+    const size_t np = (size_t)(c->M + 16) * 64;
+    int rc;
+    if ((rc = c->dalloc(&Cp, np)) || (rc = c->dalloc(&rec, c->h_rec.size()))) return rc;
+    if (mixed && ((rc = c->dalloc(&Cpf, np)) || (rc = c->dalloc(&Cf, (size_t)c->M * c->n_occ)))) return rc;
+    P = c->own;
+    P.Cp = Cp;
+    P.Cpf = Cpf;
+    P.Cf = Cf;
+    P.mo.rec = P.j16.rec = P.j32.rec = rec;   // (a tile's first record counts from the common base)
     return VMC_OK;
 }
 
@@ -802,7 +855,7 @@ static int setup_ecp(vmc_ctx *c, const vmc_ecp *e, int A) {
 
 static int setup_body_jastrow(vmc_ctx *c, const vmc_jastrow *jas, int A) {
     int rc;
-    if ((rc = upload_basis(c, jas->jas_basis, A, c->jdev, c->jtiles16, &c->jtiles32))) return rc;
+    if ((rc = upload_basis(c, jas->jas_basis, A, c->jdev, c->own.j16, &c->own.j32))) return rc;
     const int MJ = c->MJ, nq = c->nq;
     std::vector<double> blk((size_t)nq * MJ * 64, 0.0);
     for (int q = 0; q < nq; ++q)
@@ -939,19 +992,20 @@ int vmc_init(const vmc_basis *basis, const vmc_nuclei *nuclei, const vmc_mo *mo,
     // ---- fold normalisation, upload the basis tables -----------------------
     int rc;
     if ((rc = set_device(c))) return bail(rc);
-    if ((rc = upload_basis(c, basis, A, c->bdev, c->tiles16))) return bail(rc);
+    if ((rc = upload_basis(c, basis, A, c->bdev, c->own.mo))) return bail(rc);
     if ((rc = c->upload(&c->d_C, mo->C, (size_t)M * c->n_occ)) || (rc = c->upload(&c->d_R, nuclei->xyz, 3 * A)) ||
         (rc = c->upload(&c->d_Z, nuclei->Z, A)))
         return bail(rc);
-    if (opt->precision == VMC_MIXED) {
-        std::vector<float> cf((size_t)M * c->n_occ);
-        for (size_t k = 0; k < cf.size(); ++k) cf[k] = (float)mo->C[k];
-        if ((rc = c->upload(&c->d_Cf, cf.data(), cf.size())) || (rc = c->dalloc(&c->d_Cm, cf.size())))
-            return bail(rc);
-    }
-    if ((rc = c->dalloc(&c->d_cpad, (size_t)(std::max(M, c->MJ) + 16) * 64))) return bail(rc);
     if (c->MJ > 0 && (rc = setup_body_jastrow(c, jas, A))) return bail(rc);
     if (opt->ecp && (rc = setup_ecp(c, opt->ecp, A))) return bail(rc);
+    c->h_rec.push_back(ShellRec{});   // (the row kernels load one record ahead)
+    if ((rc = c->upload(&c->d_rec, c->h_rec.data(), c->h_rec.size())) ||
+        (rc = alloc_prepared(c, c->user, opt->precision == VMC_MIXED)) ||
+        (rc = alloc_prepared(c, c->own, opt->precision == VMC_MIXED)) ||
+        (rc = prepare(c, c->own, c->d_C, c->d_R, nullptr)))
+        return bail(rc);
+    // (the calls may come on streams that do not wait for the default one)
+    if (hipStreamSynchronize(nullptr) != hipSuccess) return bail(c->fail(VMC_EDEVICE, "hipStreamSynchronize failed"));
 
     SysDev &sd = c->sys;
     sd.N = c->N;
@@ -1131,8 +1185,8 @@ int vmc_sweep(vmc_ctx *c, double *walkers, int64_t W, int32_t nsteps, uint64_t s
         const uint32_t sidx = (uint32_t)(sweep_offset + t);
         uint8_t *acc_t = accept ? accept + (size_t)t * c->N * W : nullptr;
         if ((rc = c->opt.precision == VMC_MIXED
-                      ? sweep_once<float>(c, walkers, W, t, sidx, seed, acc_t, c->d_Cf, st)
-                      : sweep_once<double>(c, walkers, W, t, sidx, seed, acc_t, c->d_C, st)))
+                      ? sweep_once<float>(c, walkers, W, t, sidx, seed, acc_t, st)
+                      : sweep_once<double>(c, walkers, W, t, sidx, seed, acc_t, st)))
             return rc;
         if (!(flags & VMC_SWEEP_MEASURE)) continue;
         c->ecp_rot = sidx;
@@ -1290,6 +1344,7 @@ int vmc_measure(vmc_ctx *c, const double *walkers, int64_t W, const double *C, c
     int rc;
     if ((rc = set_device(c))) return rc;
     hipStream_t st = (hipStream_t)stream;
+    if ((rc = prepare(c, c->user, C, R, st))) return rc;
     const int full = (out->dEL_dR || out->dlnpsi_dR || out->dlnjac_dR || out->O || out->G) ? 1 : 0;
     const int warp = (R != R0) ? 1 : 0;
     const int64_t Mn = (int64_t)c->M * c->n_occ, A3 = 3 * c->A;
@@ -1301,7 +1356,7 @@ int vmc_measure(vmc_ctx *c, const double *walkers, int64_t W, const double *C, c
                     off(out->dEL_dR, A3), off(out->dlnpsi_dR, A3), off(out->dlnjac_dR, A3),
                     off(out->O, Mn),      off(out->G, Mn)};
         c->ecp_id0 = c0;
-        if ((rc = run_measure(c, walkers + c0 * c->N * 3, cw, C, R, R0, warp, full, o, st))) return rc;
+        if ((rc = run_measure(c, walkers + c0 * c->N * 3, cw, c->user, R0, warp, full, o, st))) return rc;
     }
     return VMC_OK;
 }
@@ -1340,6 +1395,7 @@ int vmc_adjoint(vmc_ctx *c, const double *walkers, int64_t W, const double *C, c
     int rc;
     if ((rc = set_device(c))) return rc;
     hipStream_t st = (hipStream_t)stream;
+    if ((rc = prepare(c, c->user, C, R, st))) return rc;
     const int64_t Mn = (int64_t)c->M * c->n_occ, A3 = 3 * c->A, nv = Mn + A3;
     HIP_OK(c, hipMemsetAsync(c->vjp_acc, 0, nv * 8, st));
     HIP_OK(c, hipMemsetAsync(c->vjp_comp, 0, nv * 8, st));
@@ -1349,7 +1405,7 @@ int vmc_adjoint(vmc_ctx *c, const double *walkers, int64_t W, const double *C, c
         const int64_t cw = std::min(step, W - c0);
         WalkerOut o{c->st_EL, c->st_lnpsi, c->st_lnjac, c->st_dEdR, c->st_dPdR, c->st_dJdR, c->st_O, c->st_G};
         c->ecp_id0 = c0;
-        if ((rc = run_measure(c, walkers + c0 * c->N * 3, cw, C, R, R0, warp, 1, o, st))) return rc;
+        if ((rc = run_measure(c, walkers + c0 * c->N * 3, cw, c->user, R0, warp, 1, o, st))) return rc;
         EstArgs a{c->st_EL, c->st_dEdR, c->st_dPdR, c->st_dJdR, c->st_O, c->st_G, nullptr,
                   gEL + c0, gPsi + c0,  gJac + c0,  A3,         Mn};
         HIP_OK(c, vmcx::launch_reduce(a, 1, nv, cw, c->partial, MAX_SEG, c->vjp_acc, c->vjp_comp, nullptr, nullptr,

@@ -8,6 +8,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace vmcx {
 
 // ---------------------------------------------------------------------------
@@ -91,6 +93,31 @@ struct BasisDev {
     const int *atom_ao;      // [M]
 };
 
+// One shell as the row kernels read it: everything a wavefront that evaluates
+// the shell at 64 rows needs, in 128 contiguous bytes (scalar loads issued
+// together instead of a chain through the tables above).  al, cp: the first
+// three exponents and coefficients; alf, cpf the same rounded to FP32; lnp =
+// l | number of primitives << 8; dmu = the shell's first AO within its tile.
+constexpr int REC_PRIM = 3;
+struct alignas(128) ShellRec {
+    double x, y, z;
+    double alf[REC_PRIM];
+    float cpf[REC_PRIM];
+    int lnp, dmu, p0, atom;
+    double al[REC_PRIM], cp[REC_PRIM];
+};
+
+// Tiles of consecutive whole shells.  hdr[t] = (first AO, AOs, first record,
+// packed counts): the tile's records are ordered by the wavefront that
+// evaluates them, byte v of the packed word being the end of wavefront v's.
+typedef int TileHdr __attribute__((ext_vector_type(4)));
+struct ShellTiles {
+    const TileHdr *hdr;
+    const ShellRec *rec;
+    int n_tiles;
+    const double *prim_exp, *prim_cp;
+};
+
 // Monomial exponents of cartesian component q of a shell with angular
 // momentum l, in the order s; x,y,z; xx,xy,xz,yy,yz,zz (packed a | b<<4 | c<<8).
 __host__ __device__ inline int cart_pow(int l, int q) {
@@ -168,11 +195,13 @@ __host__ __device__ inline void ao_components(T x, T y, T z, T rho, T R0, T R1, 
     const T Pzz = T(c * (c - 1)) * xa * yb * tpow(z, c - 2);
     const T lapP = Pxx + Pyy + Pzz;
     const T two = T(2);
-    out[1] = eta * (Px * R0 + two * x * P * R1);
-    out[2] = eta * (Py * R0 + two * y * P * R1);
-    out[3] = eta * (Pz * R0 + two * z * P * R1);
+    // (sums of products as explicit FMAs: which product of a sum the compiler
+    // rounds by itself otherwise changes with the code around it)
+    out[1] = eta * fma(two * x * P, R1, Px * R0);
+    out[2] = eta * fma(two * y * P, R1, Py * R0);
+    out[3] = eta * fma(two * z * P, R1, Pz * R0);
     // lap[P R(rho)] = lapP R + 4 (x.gradP) R' + P (6 R' + 4 rho R''), x.gradP = l P
-    out[4] = eta * (lapP * R0 + T(4 * l + 6) * P * R1 + T(4) * rho * P * R2);
+    out[4] = eta * fma(T(4) * rho * P, R2, fma(T(4 * l + 6) * P, R1, lapP * R0));
     if (NC == 5) return;
     const T Pxy = T(a * b) * tpow(x, a - 1) * tpow(y, b - 1) * zc;
     const T Pxz = T(a * c) * tpow(x, a - 1) * yb * tpow(z, c - 1);
@@ -373,45 +402,143 @@ __device__ inline double wave_sum_dpp(double v) {
     return (r[0] + r[1]) + (r[2] + r[3]);
 }
 
-// All cartesian components of shell s at an electron, with the angular
-// momentum fixed at compile time so that every component index is a constant
-// and nothing lands in per-lane scratch: stored straight to dst[q*NC + k] (LDS
-// or registers).  The displacement is formed in FP64 and rounded to T.
+// All cartesian components of a shell at an electron, with the angular
+// momentum fixed at compile time so that every component index (and the
+// component factor: 1/sqrt(3) for xx, yy, zz, else 1) is a constant and nothing
+// lands in per-lane scratch: stored straight to dst[q*NC + k] (LDS or
+// registers).
 template <int NC, typename T, int L>
-__device__ inline void shell_components(const BasisDev &B, int mu0, T x, T y, T z, T rho, T R0, T R1, T R2, T R3,
-                                        T *dst) {
+__device__ inline void shell_components(T x, T y, T z, T rho, T R0, T R1, T R2, T R3, T *dst) {
 #pragma unroll
     for (int q = 0; q < (L + 1) * (L + 2) / 2; ++q) {
         T o[NC];
-        ao_components<NC, T>(x, y, z, rho, R0, R1, R2, R3, cart_pow(L, q), (T)ldc(B.ao_eta + mu0 + q), o);
+        const bool sq = L == 2 && (q == 0 || q == 3 || q == 5);
+        ao_components<NC, T>(x, y, z, rho, R0, R1, R2, R3, cart_pow(L, q), sq ? T(0x1.279a74590331dp-1) : T(1), o);
 #pragma unroll
         for (int k = 0; k < NC; ++k) dst[q * NC + k] = o[k];
     }
 }
 
-// Shell s (uniform over the wavefront in the callers) at one electron per
-// lane; the basis tables and R are read with ldc.
-template <int NC, typename T>
-__device__ inline int shell_eval_to(const BasisDev &B, const double *R, int s, double rx, double ry, double rz,
-                                    T *dst) {
-    const int atom = ldc(B.shell_atom + s);
-    const double dx = rx - ldc(R + 3 * atom), dy = ry - ldc(R + 3 * atom + 1), dz = rz - ldc(R + 3 * atom + 2);
-    const double rho_d = dx * dx + dy * dy + dz * dz;
-    const T x = (T)dx, y = (T)dy, z = (T)dz;
-    const T rho = (T)rho_d;
-    T R0, R1, R2, R3;
-    shell_radial<NC, T>(B, s, rho_d, R0, R1, R2, R3);
-    const int l = ldc(B.shell_l + s), mu0 = ldc(B.shell_mu0 + s);
-    if (l == 0) {
-        shell_components<NC, T, 0>(B, mu0, x, y, z, rho, R0, R1, R2, R3, dst);
-        return 1;
+// The same evaluated in FP64 and rounded once to FP32.
+template <int NC, int L>
+__device__ inline void shell_round_l(double x, double y, double z, double rho, double R0, double R1, double R2,
+                                     double R3, float *dst) {
+    double t[(L + 1) * (L + 2) / 2 * NC];
+    shell_components<NC, double, L>(x, y, z, rho, R0, R1, R2, R3, t);
+#pragma unroll
+    for (int i = 0; i < (L + 1) * (L + 2) / 2 * NC; ++i) dst[i] = (float)t[i];
+}
+
+// The fields of a record that an evaluation in type W of the radial sums
+// reads, as wavefront-uniform values.  A wavefront loads the next record
+// before it evaluates the current one, so that the scalar loads' latency is
+// not on its path.
+template <typename W>
+struct RecVals {
+    double x, y, z, al[REC_PRIM];
+    W cp[REC_PRIM];
+    int lnp, dmu, p0, atom;
+};
+
+// A lane's displacement from the atom of the last record it evaluated: the
+// shells of an atom follow one another and share it (atom = -1: none yet).
+template <typename W>
+struct ShellDisp {
+    int atom = -1;
+    double rho_d = 0.0;
+    W x = W(0), y = W(0), z = W(0), rho = W(0);
+};
+
+template <typename W>
+__device__ inline RecVals<W> rec_load(const ShellRec *rc) {
+    RecVals<W> v;
+    v.x = ldc(&rc->x);
+    v.y = ldc(&rc->y);
+    v.z = ldc(&rc->z);
+#pragma unroll
+    for (int k = 0; k < REC_PRIM; ++k) {
+        if constexpr (sizeof(W) == 4) {
+            v.al[k] = ldc(rc->alf + k);
+            v.cp[k] = ldc(rc->cpf + k);
+        } else {
+            v.al[k] = ldc(rc->al + k);
+            v.cp[k] = ldc(rc->cp + k);
+        }
     }
-    if (l == 1) {
-        shell_components<NC, T, 1>(B, mu0, x, y, z, rho, R0, R1, R2, R3, dst);
-        return 3;
+    v.lnp = ldc(&rc->lnp);
+    v.dmu = ldc(&rc->dmu);
+    v.p0 = ldc(&rc->p0);
+    v.atom = ldc(&rc->atom);
+    return v;
+}
+
+// The shell of record rc (uniform over the wavefront) at one electron per
+// lane.  The displacement is formed in FP64 and rounded to W.  W = double
+// with T = float: radial sums in FP64 around the FP32 exponential of the split
+// argument (its relative error, ~1e-7, is the one the FP32 path has), every
+// component formed in FP64 and rounded once -- for the FP32 measurement rows:
+// components formed in FP32 from FP32 radial sums lose digits to cancellation
+// (the Laplacian near its radial nodes), and that rounding, second order
+// through the inverse, shifts the walker-averaged E_L by several 1e-6 Ha;
+// formed in FP64 and rounded once they leave a few 1e-7 Ha.
+template <int NC, typename T, typename W>
+__device__ inline void shell_rec_eval(const ShellTiles &tl, const RecVals<W> &rc, ShellDisp<W> &sd, double rx,
+                                      double ry, double rz, T *dst) {
+    if (rc.atom != sd.atom) {
+        const double dx = rx - rc.x, dy = ry - rc.y, dz = rz - rc.z;
+        sd.atom = rc.atom;
+        sd.rho_d = dx * dx + dy * dy + dz * dz;
+        sd.x = (W)dx;
+        sd.y = (W)dy;
+        sd.z = (W)dz;
+        sd.rho = (W)sd.rho_d;
     }
-    shell_components<NC, T, 2>(B, mu0, x, y, z, rho, R0, R1, R2, R3, dst);
-    return 6;
+    const double rho_d = sd.rho_d;
+    const W x = sd.x, y = sd.y, z = sd.z, rho = sd.rho;
+    const int l = rc.lnp & 255, np = rc.lnp >> 8;
+    W R0 = W(0), R1 = W(0), R2 = W(0), R3 = W(0);
+    auto prim = [&](double ad, W cp) {
+        // the exponent in the type of the sums, used alike in the exponential
+        // and in the derivative factors, so that value and derivatives belong
+        // to one function
+        const W al = (W)ad;
+        W e;
+        if constexpr (sizeof(T) == 4)
+            e = cp * (W)exp_neg(ad, rho_d, 0.0f);
+        else
+            e = cp * exp_neg(ad, rho_d, 0.0);
+        R0 += e;
+        if constexpr (NC > 1) {
+            R1 -= al * e;
+            R2 += al * al * e;
+        }
+    };
+    if (np == REC_PRIM) {
+#pragma unroll
+        for (int k = 0; k < REC_PRIM; ++k) prim(rc.al[k], rc.cp[k]);
+    } else {
+        prim(rc.al[0], rc.cp[0]);
+        if (np > 1) prim(rc.al[1], rc.cp[1]);
+        if (np > REC_PRIM) prim(rc.al[2], rc.cp[2]);
+        for (int k = REC_PRIM; k < np; ++k)
+            prim((double)(W)ldc(tl.prim_exp + rc.p0 + k), (W)ldc(tl.prim_cp + rc.p0 + k));
+    }
+    dst += rc.dmu * NC;
+    if constexpr (sizeof(W) > sizeof(T)) {
+        if (l == 0)
+            shell_round_l<NC, 0>(x, y, z, rho, R0, R1, R2, R3, dst);
+        else if (l == 1)
+            shell_round_l<NC, 1>(x, y, z, rho, R0, R1, R2, R3, dst);
+        else
+            shell_round_l<NC, 2>(x, y, z, rho, R0, R1, R2, R3, dst);
+    } else {
+        if (l == 0)
+            shell_components<NC, T, 0>(x, y, z, rho, R0, R1, R2, R3, dst);
+        else if (l == 1)
+            shell_components<NC, T, 1>(x, y, z, rho, R0, R1, R2, R3, dst);
+        else
+            shell_components<NC, T, 2>(x, y, z, rho, R0, R1, R2, R3, dst);
+    }
 }
 
 // 1/sqrt(x) and 1/x (x > 0) in FP64: the hardware estimate refined by two

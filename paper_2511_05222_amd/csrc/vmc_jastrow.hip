@@ -46,22 +46,26 @@ constexpr int JAS_ELEC = 128;  // electrons
 // tile, which the block then writes row by row (consecutive threads,
 // consecutive functions).
 template <typename T, int NC, int MT>
-__global__ __launch_bounds__(256) void k_jas_values(BasisDev JB, AoTiles tiles, const double *__restrict__ R,
-                                                    const double *__restrict__ pos, int64_t rows,
-                                                    T *__restrict__ out, T *__restrict__ der) {
+__global__ __launch_bounds__(256) void k_jas_values(int MJ, ShellTiles tiles, const double *__restrict__ pos,
+                                                    int64_t rows, T *__restrict__ out, T *__restrict__ der) {
     constexpr int RB = 64, TS = MT * NC + 1;
-    __shared__ double sp[RB * 3];
     __shared__ T tv[RB * TS];
-    const int tid = threadIdx.x, MJ = JB.n_ao;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t row0 = (int64_t)blockIdx.x * RB;
-    for (int k = tid; k < RB * 3; k += 256) sp[k] = (row0 + k / 3) < rows ? pos[row0 * 3 + k] : 0.0;
+    const double *pr = pos + 3 * min(row0 + lane, rows - 1);
+    const double px = pr[0], py = pr[1], pz = pr[2];
+    const int turn = (wave + (int)blockIdx.x) & 3;
+    ShellDisp<T> sd;
     for (int tile = 0; tile < tiles.n_tiles; ++tile) {
-        const int s0 = tiles.s0[tile], s1 = tiles.s1[tile], mu0 = tiles.mu0[tile], nmu = tiles.mu1[tile] - mu0;
+        const TileHdr hd = ldc(tiles.hdr + tile);
+        const int mu0 = hd.x, nmu = hd.y;
         __syncthreads();
-        for (int p = tid; p < RB * (s1 - s0); p += 256) {
-            const int s = __builtin_amdgcn_readfirstlane(s0 + p / RB), r = p % RB;
-            shell_eval_to<NC, T>(JB, R, s, sp[3 * r], sp[3 * r + 1], sp[3 * r + 2],
-                                 tv + r * TS + (ldc(JB.shell_mu0 + s) - mu0) * NC);
+        const int q1 = (hd.w >> (8 * turn)) & 255, q0 = turn ? (hd.w >> (8 * turn - 8)) & 255 : 0;
+        RecVals<T> rc = rec_load<T>(tiles.rec + hd.z + q0);
+        for (int q = q0; q < q1; ++q) {
+            const RecVals<T> cur = rc;
+            rc = rec_load<T>(tiles.rec + hd.z + q + 1);   // (one record past the last is there)
+            shell_rec_eval<NC, T, T>(tiles, cur, sd, px, py, pz, tv + lane * TS);
         }
         __syncthreads();
         for (int p = tid; p < RB * nmu; p += 256) {
@@ -469,21 +473,21 @@ __global__ __launch_bounds__(256) void k_jas_adjoint(BasisDev JB, const double *
 }
 
 template <typename T>
-hipError_t launch_jas_values(const BasisDev &JB, const AoTiles &jt, const double *R, const double *pos, int64_t rows,
-                             T *out, hipStream_t st, T *der, const AoTiles *jt32) {
+hipError_t launch_jas_values(int MJ, const Prepared &P, const double *pos, int64_t rows, T *out, hipStream_t st,
+                             T *der) {
     if (rows < 1) return hipSuccess;
     const dim3 g((unsigned)((rows + 63) / 64));
     // (wider tiles: half the barriers and row segments twice as long; the
     // FP64 tile of 32 functions would not fit the static LDS)
     if constexpr (sizeof(T) == sizeof(float))
-        if (der && jt32) {
-            hipLaunchKernelGGL((k_jas_values<T, 5, 32>), g, dim3(256), 0, st, JB, *jt32, R, pos, rows, out, der);
+        if (der) {
+            hipLaunchKernelGGL((k_jas_values<T, 5, 32>), g, dim3(256), 0, st, MJ, P.j32, pos, rows, out, der);
             return hipGetLastError();
         }
     if (der)
-        hipLaunchKernelGGL((k_jas_values<T, 5, 16>), g, dim3(256), 0, st, JB, jt, R, pos, rows, out, der);
+        hipLaunchKernelGGL((k_jas_values<T, 5, 16>), g, dim3(256), 0, st, MJ, P.j16, pos, rows, out, der);
     else
-        hipLaunchKernelGGL((k_jas_values<T, 1, 16>), g, dim3(256), 0, st, JB, jt, R, pos, rows, out, der);
+        hipLaunchKernelGGL((k_jas_values<T, 1, 16>), g, dim3(256), 0, st, MJ, P.j16, pos, rows, out, der);
     return hipGetLastError();
 }
 
@@ -541,8 +545,8 @@ hipError_t launch_jas_adjoint(const BasisDev &JB, const double *R, int N, int64_
 }
 
 #define JAS_INST(T)                                                                                               \
-    template hipError_t launch_jas_values<T>(const BasisDev &, const AoTiles &, const double *, const double *,   \
-                                             int64_t, T *, hipStream_t, T *, const AoTiles *);                     \
+    template hipError_t launch_jas_values<T>(int, const Prepared &, const double *, int64_t, T *, hipStream_t,     \
+                                             T *);                                                                 \
     template hipError_t launch_jas_vprod<T>(int, int, int64_t, const T *, const T *, const T *, T *,             \
                                             hipStream_t);                                                          \
     template hipError_t launch_jas_assemble<T>(int, int, int, int64_t, int64_t, int, const T *, const T *,        \

@@ -360,16 +360,6 @@ hipError_t launch_finalize(const SysDev &S, const double *R, const double *R0, c
     return hipGetLastError();
 }
 
-__global__ void k_round_f32(const double *__restrict__ x, float *__restrict__ y, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) y[i] = (float)x[i];
-}
-
-hipError_t launch_round_f32(const double *x, float *y, int64_t n, hipStream_t st) {
-    hipLaunchKernelGGL(k_round_f32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, x, y, n);
-    return hipGetLastError();
-}
-
 // The k walkers with the largest keys, by a most-significant-digit radix
 // select on the bit patterns of the keys (non-negative doubles order like
 // their bits; NaN counts as +inf), 8 bits per pass, then a pass over index

@@ -5,11 +5,17 @@
 
 namespace vmcx {
 
-// AO tiles: consecutive whole shells (at most 16 AOs each for k_mo_rows_mfma).
-struct AoTiles {
-    const int *s0, *s1, *mu0, *mu1;
-    int n_tiles;
+// The MO coefficients and nuclei of a launch as the kernels read them
+// (launch_prepare): C and its padded copy [M + 16][64] in FP64 and, in mixed
+// precision, FP32; the shells' records at the nuclei R in tiles of at most 16
+// AOs (mo) and, of the Jastrow basis, 16 and 32 functions (j16, j32).
+struct Prepared {
+    const double *C = nullptr, *Cp = nullptr, *R = nullptr;
+    const float *Cf = nullptr, *Cpf = nullptr;
+    ShellTiles mo{}, j16{}, j32{};
 };
+hipError_t launch_prepare(const double *C, int M, int n, const double *R, const ShellRec *src, int n_rec, double *Cp,
+                          float *Cpf, float *Cf, ShellRec *rec, hipStream_t st);
 
 // LDS layout of k_sweep_r (bytes): wpb wavefront regions of two broadcast
 // vectors each.
@@ -140,16 +146,14 @@ hipError_t launch_ecp_adjoint(const SysDev &S, const EcpDev &E, const T *C, cons
                               int W, const EcpBufs<T> &eb, const T *ktil, double *G, float *Gf, double *dedr,
                               const EcpJas<T> &J, hipStream_t st);
 
-// cpad: scratch of (M + 16) * 64 elements for the padded copy of C (n_occ <= 64);
-// rows_dev (optional): a device count that caps n_rows
+// rows_dev (optional): a device count that caps n_rows (n_occ <= 64)
 template <typename T>
-hipError_t launch_mo_rows_mfma(const SysDev &S, const T *C, const double *R, const double *pos, int64_t n_rows,
-                               const AoTiles &tiles16, T *out, int nc, T *cpad, hipStream_t st,
-                               const int *rows_dev = nullptr);
+hipError_t launch_mo_rows_mfma(const SysDev &S, const Prepared &P, const double *pos, int64_t n_rows, T *out, int nc,
+                               hipStream_t st, const int *rows_dev = nullptr);
 // One-/three-body Jastrow terms (vmc_jastrow.hip).  jas_values: out[row][mu]
 // = chi_mu(pos[row]) and, with der, der[row][c][mu] its gradient (c < 3) and
-// Laplacian (c = 3) (in FP32 over the tiles of <= 32 functions jt32 when
-// given, else jt's of <= 16).  jas_vprod: the products of the rows of X (of X - X0
+// Laplacian (c = 3) (in FP32 over the tiles of <= 32 functions, else over
+// those of <= 16).  jas_vprod: the products of the rows of X (of X - X0
 // when X0 is given) with [xi3 | xi1] ([nq][MJ][64] in xiblk), MJ + 1 columns:
 // in blocks of 64, V[q][row][64] (X), or row by row with a row stride of
 // MJ + 1 rounded up to a multiple of 4 (X - X0).
@@ -158,8 +162,8 @@ hipError_t launch_mo_rows_mfma(const SysDev &S, const T *C, const double *R, con
 // lap chi / 2, abar from gb).  jas_adjoint: its terms of dE_L/dr_e (added to
 // dedr) and the per-function sums jtao.
 template <typename T>
-hipError_t launch_jas_values(const BasisDev &JB, const AoTiles &jt, const double *R, const double *pos, int64_t rows,
-                             T *out, hipStream_t st, T *der = nullptr, const AoTiles *jt32 = nullptr);
+hipError_t launch_jas_values(int MJ, const Prepared &P, const double *pos, int64_t rows, T *out, hipStream_t st,
+                             T *der = nullptr);
 template <typename T>
 hipError_t launch_jas_vprod(int MJ, int nq, int64_t rows, const T *X, const T *X0, const T *xiblk, T *V,
                             hipStream_t st);
@@ -234,7 +238,6 @@ int sweep_blocks_per_cu(int n_occ, int wpb, size_t lds);
 // list[0..k) = the k walkers of W with the largest keys (ties to the lower
 // index), in index order
 hipError_t launch_promote_select(const double *key, int W, int k, int *list, hipStream_t st);
-hipError_t launch_round_f32(const double *x, float *y, int64_t n, hipStream_t st);
 
 hipError_t launch_gather_rows(const double *src, const int *list, int64_t kc, int64_t len, double *dst,
                               hipStream_t st);
