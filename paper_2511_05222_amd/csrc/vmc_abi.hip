@@ -218,7 +218,8 @@ static void prof_end(vmc_ctx *c, int k, int idx, hipStream_t st) {
 }
 
 // LDS layout of the sweep for an arithmetic type of ts bytes and blocks of
-// wpb walkers: two broadcast vectors per wavefront.
+// wpb walkers: two broadcast vectors, the rebuild's workspace and the moves'
+// data per wavefront.
 static SweepLayout sweep_layout(const vmc_ctx *c, size_t ts, int wpb) {
     SweepLayout s{};
     auto al = [](size_t b) { return (int)((b + 15) & ~(size_t)15); };
@@ -228,6 +229,10 @@ static SweepLayout sweep_layout(const vmc_ctx *c, size_t ts, int wpb) {
     w += al((size_t)kn * ts);
     s.off_colj = (int)w;
     w += al((size_t)kn * ts);
+    s.off_ws = (int)w;
+    w += al((size_t)vmcx::sweep_ws(c->n_occ, ts == sizeof(float)));
+    s.off_mv = (int)w;
+    w += al((size_t)c->N * 7 * 8);
     s.wave_bytes = (int)w;
     s.wpb = wpb;
     s.bytes = (size_t)wpb * w;

@@ -71,50 +71,67 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     bool bad = false;
     if (wave < 2) {
         const int b = wave, off = b ? nu : 0, nb = b ? nd : nu;
-        // B = A^T of the block: lane c holds orbital c at the block's electrons
-        int lz = lane;
-        asm volatile("" : "+v"(lz));
-        int sig;
+        double *K = Ks + (size_t)b * KN * ldk;
+        int *pm = perm + 64 * b;
         double la = 0.0;
-        double Br[KN];
         const bool from_state = mb.kst != nullptr && mb.kstale[2 * w + b] == 0;
         if (from_state) {
-            // the sweep's inverse, in its register layout
+            // the sweep's inverse, in its register layout: lane p_k holds
+            // column k with register j = orbital p_j
             const T *kk = mb.kst + ((size_t)w * 2 + b) * KN * KN + min(lane, KN - 1);
+            T kr[KN];
 #pragma unroll
-            for (int r = 0; r < KN; ++r) {
-                const double v = (double)kk[r * KN];
-                Br[r] = lane < KN ? v : 0.0;
-            }
-            const int sg = (int)mb.ksig[((size_t)w * 2 + b) * KN + min(lane, KN - 1)];
-            sig = lane < KN ? sg : lane;
+            for (int r = 0; r < KN; ++r) kr[r] = kk[r * KN];
+            const int sig = (int)mb.ksig[((size_t)w * 2 + b) * KN + min(lane, KN - 1)];
+            if (lane < KN) pm[sig] = lane;
+            wave_sync_s();
+            if (lane < KN)
+#pragma unroll
+                for (int j = 0; j < KN; ++j) K[pm[j] * ldk + sig] = (double)kr[j];
         } else {
-            // (clamped, unconditional loads: a guarded load per register would
-            // be issued and waited for one at a time)
-            const T *pa = ph + (size_t)off * 5 * n + min(lz, nb - 1);
-            T av[KN];
+            // B = A^T of the block in the layout of gj_regs (clamped,
+            // unconditional loads: a guarded load per register would be issued
+            // and waited for one at a time)
+            constexpr int CC = KN / 4;
+            int lz = lane;
+            asm volatile("" : "+v"(lz));
+            const int m = lz & 15, g = lz >> 4;
+            T av[RTS * CC];
 #pragma unroll
-            for (int r = 0; r < KN; ++r) av[r] = pa[(size_t)min(r, nb - 1) * 5 * n];
+            for (int q = 0; q < CC; ++q)
+#pragma unroll
+                for (int s = 0; s < RTS; ++s)
+                    av[s * CC + q] = ph[(size_t)(off + min(4 * q + g, nb - 1)) * 5 * n + min(m + 16 * s, nb - 1)];
+            double Br[RTS * CC];
             double mx = 0.0;
 #pragma unroll
-            for (int r = 0; r < KN; ++r) {
-                const bool in = lz < nb && r < nb;
-                Br[r] = in ? (double)av[r] : ((lz == r) ? 1.0 : 0.0);   // identity padding
-                mx = fmax(mx, in ? fabs(Br[r]) : 0.0);
+            for (int s = 0; s < RTS; ++s)
+#pragma unroll
+                for (int q = 0; q < CC; ++q) {
+                    const int c = m + 16 * s, k = 4 * q + g;
+                    const bool in = c < nb && k < nb;
+                    const double v = in ? (double)av[s * CC + q] : (c == k ? 1.0 : 0.0);   // identity padding
+                    Br[s * CC + q] = v;
+                    mx = fmax(mx, in ? fabs(v) : 0.0);
+                }
+            int sg[RTS];
+            gj_regs<KN, true>(Br, sg, bad, la, gj_tol(mx), K);   // (K's place in LDS is still free)
+            // natural layout: row p_k holds column k, its column j orbital p_j
+            if (g == 0)
+#pragma unroll
+                for (int s = 0; s < RTS; ++s) pm[sg[s]] = m + 16 * s;
+            wave_sync_s();
+#pragma unroll
+            for (int q = 0; q < CC; ++q) {
+                const int row = pm[4 * q + g] * ldk;
+#pragma unroll
+                for (int s = 0; s < RTS; ++s) K[row + sg[s]] = Br[s * CC + q];
             }
-            gj_regs<KN, true>(Br, sig, bad, la, gj_tol(mx));
         }
         if (lane == 0) {
             red[4 + b] = la;
             red[8 + b] = from_state ? 1.0 : 0.0;
         }
-        // natural layout: lane p_k holds column k with register j = orbital p_j
-        if (lane < KN) perm[64 * b + sig] = lane;
-        wave_sync_s();
-        double *K = Ks + (size_t)b * KN * ldk;
-        if (lane < KN)
-#pragma unroll
-            for (int j = 0; j < KN; ++j) K[perm[64 * b + j] * ldk + sig] = Br[j];
     }
     // Jastrow and potential, each electron pair once.  Round s pairs electron
     // e with k = (e + s) mod N; rounds 1 .. N/2 cover every pair once (in

@@ -18,9 +18,9 @@ hipError_t launch_prepare(const double *C, int M, int n, const double *R, const 
                           float *Cpf, float *Cf, ShellRec *rec, hipStream_t st);
 
 // LDS layout of k_sweep_r (bytes): wpb wavefront regions of two broadcast
-// vectors each.
+// vectors, the rebuild's workspace and the moves' data each.
 struct SweepLayout {
-    int off_phin, off_colj;                         // within a wavefront region
+    int off_phin, off_colj, off_ws, off_mv;         // within a wavefront region
     int wave_bytes;
     int wpb;                                        // walkers (wavefronts) per block
     size_t bytes;                                   // per block
@@ -205,6 +205,7 @@ struct KState {
 };
 
 int sweep_kn(int n_occ);
+int sweep_ws(int n_occ, bool f32);
 // prop[w][e] = walkers[w][e] + sigma z_e for the W walkers (Philox normals of
 // the sweep)
 hipError_t launch_propose(const double *walkers, int64_t W, int N, uint32_t sweep, uint64_t seed, double sigma,

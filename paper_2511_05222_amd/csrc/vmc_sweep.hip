@@ -10,10 +10,13 @@
 //   k_sweep_r      the moves in order, per walker: ratio, Jastrow difference,
 //                  accept, Sherman-Morrison update, refreshes.
 // k_sweep_r runs one wavefront per walker, L.wpb walkers per block.  Per
-// wavefront in LDS: two broadcast vectors.  Everything else of the walker
-// lives in registers:
-//   * positions and proposals: lane l holds electrons l and l + 64;
-//   * the uniforms of this sweep: lane l holds those of electrons l and l + 64;
+// wavefront in LDS: two broadcast vectors, the rebuild's workspace and, read
+// uniformly by the moves, every electron's start position, proposal and
+// uniform of this sweep (held in registers they cost a dozen lane reads a move
+// and spills; as scalar loads their waits fell into the LDS waits: 5.3 against
+// 4.7 ms per 65536-walker FP32 launch with two rebuilds, 21 atoms).  Everything
+// else of the walker lives in registers:
+//   * the current positions: lane l holds electrons l and l + 64;
 //   * the inverse K of the spin block being swept: KN registers per lane,
 //     lane p_k holding column k (electron k of the block), register r holding
 //     orbital p_r, where p is the pivot order of the last rebuild (gj_regs).
@@ -33,10 +36,16 @@
 namespace vmcx {
 
 // Rebuild the inverse of spin block [off, off + nb) from the walker's MO
-// matrix Aw ([N][n], type T) into Kr, in the layout of gj_regs.
+// matrix Aw ([N][n], type T) into Kr, one row of gj_regs' result to a lane.
+// ws: the wavefront's LDS (rebuild_ws_bytes).
 template <typename T, int KN>
-__device__ inline void rebuild(const T *Aw, int n, int off, int nb, T (&Kr)[KN], int &sig, bool &bad) {
-    const int lane = threadIdx.x & 63;
+constexpr int rebuild_ws_bytes() {
+    return gj_ws_bytes<KN>() > gj_row_bytes<T, KN>() ? gj_ws_bytes<KN>() : gj_row_bytes<T, KN>();
+}
+
+template <typename T, int KN>
+__device__ inline void rebuild(const T *Aw, int n, int off, int nb, T (&Kr)[KN], int &sig, bool &bad, void *ws) {
+    constexpr int RR = KN / 16, CC = KN / 4;
     // Rows of A were written by this wavefront (and only by it): its loads go
     // through the same L1, so a workgroup fence, which waits for the stores,
     // is enough.  An agent fence writes back and invalidates the XCD's whole
@@ -44,28 +53,35 @@ __device__ inline void rebuild(const T *Aw, int n, int off, int nb, T (&Kr)[KN],
     // (21 atoms, average over the refresh period), 0.89 instead of 0.35 ms per
     // 16384-walker FP64 launch (9 atoms).
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-    // an opaque copy of the lane id keeps the KN padding values from being
+    // an opaque copy of the lane id keeps the padding values from being
     // hoisted out of the sweep loop (they would stay live in registers)
-    int lz = lane;
+    int lz = threadIdx.x & 63;
     asm volatile("" : "+v"(lz));
+    const int m = lz & 15, g = lz >> 4;
     // (clamped, unconditional loads: a guarded load per register would be
     // issued and waited for one at a time)
-    const T *pa = Aw + (size_t)off * n + min(lz, nb - 1);
-    T av[KN];
+    T av[RR * CC];
 #pragma unroll
-    for (int r = 0; r < KN; ++r) av[r] = pa[(size_t)min(r, nb - 1) * n];
-    double Br[KN];
+    for (int q = 0; q < CC; ++q)
+#pragma unroll
+        for (int s = 0; s < RR; ++s)
+            av[s * CC + q] = Aw[(size_t)(off + min(4 * q + g, nb - 1)) * n + min(m + 16 * s, nb - 1)];
+    double Br[RR * CC];
     double mx = 0.0;
 #pragma unroll
-    for (int r = 0; r < KN; ++r) {
-        const bool in = lz < nb && r < nb;
-        Br[r] = in ? (double)av[r] : ((lz == r) ? 1.0 : 0.0);   // padding
-        mx = fmax(mx, in ? fabs(Br[r]) : 0.0);
-    }
-    double la;
-    gj_regs<KN, false>(Br, sig, bad, la, gj_tol(mx));
+    for (int s = 0; s < RR; ++s)
 #pragma unroll
-    for (int r = 0; r < KN; ++r) Kr[r] = (T)Br[r];
+        for (int q = 0; q < CC; ++q) {
+            const int c = m + 16 * s, k = 4 * q + g;
+            const bool in = c < nb && k < nb;
+            const double v = in ? (double)av[s * CC + q] : (c == k ? 1.0 : 0.0);   // padding
+            Br[s * CC + q] = v;
+            mx = fmax(mx, in ? fabs(v) : 0.0);
+        }
+    double la;
+    int sg[RR];
+    gj_regs<KN, false>(Br, sg, bad, la, gj_tol(mx), (double *)ws);
+    gj_to_rows<T, KN>(Br, sg, Kr, sig, (T *)ws);
 }
 
 // Proposals of one sweep: prop[w][e] = r_e + sigma z_e, z_e the Philox
@@ -135,7 +151,8 @@ __device__ inline double jastrow_delta(const SysDev &S, int N, int e, int lane, 
 }
 
 // FP32 with KN <= 48 fits three wavefronts per SIMD (spilling a little in the
-// FP64 rebuild); the rest runs two.
+// FP64 rebuild); the rest runs two at least (FP64 with KN = 48 at three spills
+// in the moves: 3.76 against 2.89 ms per 16384-walker launch, 21 atoms).
 template <typename T, int KN>
 constexpr int sweep_waves() {
     return (sizeof(T) == 4 && KN <= 48) ? 3 : 2;
@@ -168,7 +185,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sweep_waves
     KState<T> ks, int fresh, uint32_t sweep, uint64_t seed, int refresh_period, uint8_t *accept, int *status,
     SweepLayout L, JasSweep<T> js) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int N = S.N, nu = S.n_up, n = S.n_occ;
     const int w = blockIdx.x * (int)(blockDim.x >> 6) + wave;
     if (w >= W) return;   // no block barrier in this kernel
@@ -179,9 +196,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sweep_waves
     const double *pp = prop + (size_t)w * N * 3;
     const T *phw = Phip + (size_t)w * N * n;
     T *Aw = Amo + (size_t)w * N * n;
-    // positions, proposals and this sweep's uniforms: lane l holds electrons
-    // l and l + 64
-    double px[2], py[2], pz[2], qx[2], qy[2], qz[2], du[2];
+    // positions: lane l holds electrons l and l + 64; in LDS, read uniformly by
+    // the move of electron e, mv[e] = its start position, its proposal and its
+    // uniform
+    double px[2], py[2], pz[2];
+    double *mv = (double *)(wbase + L.off_mv);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const int e = lane + 64 * h;
@@ -190,11 +209,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sweep_waves
         px[h] = on ? wp[3 * e] : 0.0;
         py[h] = on ? wp[3 * e + 1] : 0.0;
         pz[h] = on ? wp[3 * e + 2] : 0.0;
-        qx[h] = pp[3 * ec];
-        qy[h] = pp[3 * ec + 1];
-        qz[h] = pp[3 * ec + 2];
-        du[h] = move_uniform(seed, (uint32_t)w, sweep, (uint32_t)ec);
+        const double u = move_uniform(seed, (uint32_t)w, sweep, (uint32_t)ec);
+        if (on) {
+            mv[7 * e] = px[h];
+            mv[7 * e + 1] = py[h];
+            mv[7 * e + 2] = pz[h];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) mv[7 * e + 3 + d] = pp[3 * e + d];
+            mv[7 * e + 6] = u;
+        }
     }
+    wave_sync_s();
     bool bad = false;
     T Kr[KN];
     int sig = lane;
@@ -237,6 +262,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sweep_waves
     // ahead, so that the load overlaps the move before)
     T ph_next = lane < nu ? phw[lane] : T(0);
     bool need = true;
+    int due = refresh_period;
     for (int e = 0; e < N; ++e) {
         const int b = e < nu ? 0 : 1;
         const int off = b ? nu : 0;
@@ -244,6 +270,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sweep_waves
         const int nb = b ? S.n_dn : nu;
         T *kst = ks.K + ((size_t)w * 2 + b) * KN * KN;
         if (jj == 0) {
+            // moves of the block until its next rebuild, counted over the sweeps
+            due = refresh_period - (int)((uint64_t)sweep * (uint64_t)nb % (uint64_t)refresh_period);
             // the block's inverse: rebuilt, or as left at its last move
             need = fresh || ks.stale[2 * w + b] != 0;
             if (!need) {
@@ -258,17 +286,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sweep_waves
             }
         }
         if (need) {
-            rebuild<T, KN>(Aw, n, off, nb, Kr, sig, bad);
+            rebuild<T, KN>(Aw, n, off, nb, Kr, sig, bad, wbase + L.off_ws);
             need = false;
         }
         const int src = e & 63, h = e >> 6;
-        const double u = readlane_d(h ? du[1] : du[0], src);
-        const double ex = readlane_d(h ? px[1] : px[0], src);
-        const double ey = readlane_d(h ? py[1] : py[0], src);
-        const double ez = readlane_d(h ? pz[1] : pz[0], src);
-        const double rx = readlane_d(h ? qx[1] : qx[0], src);
-        const double ry = readlane_d(h ? qy[1] : qy[0], src);
-        const double rz = readlane_d(h ? qz[1] : qz[0], src);
+        const double *me = mv + 7 * e;
+        const double ex = me[0], ey = me[1], ez = me[2], rx = me[3], ry = me[4], rz = me[5], u = me[6];
         // phi_i(r') of lane i (zero from nb on); the next move's row in flight
         const T ph = ph_next;
         if (e + 1 < N) {
@@ -360,8 +383,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sweep_waves
         }
         if (accept != nullptr && lane == 0) accept[(size_t)e * W + w] = acc ? 1 : 0;
         // refresh_period-th move of this block: rebuild before its next move
-        const uint64_t m = (uint64_t)sweep * (uint64_t)nb + (uint64_t)jj;
-        if (((m + 1) % (uint64_t)refresh_period) == 0) need = true;
+        if (--due == 0) {
+            need = true;
+            due = refresh_period;
+        }
         if (jj == nb - 1) {
             // end of the block: keep its inverse (and a rebuild still due)
 #pragma unroll
@@ -399,6 +424,16 @@ static hipError_t launch_kn(const SysDev &S, const T *Phip, const double *prop, 
     return hipGetLastError();
 }
 
+// LDS workspace of a rebuild (bytes)
+int sweep_ws(int n_occ, bool f32) {
+    switch (sweep_kn(n_occ)) {
+        case 16: return f32 ? rebuild_ws_bytes<float, 16>() : rebuild_ws_bytes<double, 16>();
+        case 32: return f32 ? rebuild_ws_bytes<float, 32>() : rebuild_ws_bytes<double, 32>();
+        case 48: return f32 ? rebuild_ws_bytes<float, 48>() : rebuild_ws_bytes<double, 48>();
+        default: return f32 ? rebuild_ws_bytes<float, 64>() : rebuild_ws_bytes<double, 64>();
+    }
+}
+
 int sweep_kn(int n_occ) { return n_occ <= 16 ? 16 : (n_occ <= 32 ? 32 : (n_occ <= 48 ? 48 : 64)); }
 
 hipError_t launch_propose(const double *walkers, int64_t W, int N, uint32_t sweep, uint64_t seed, double sigma,
@@ -431,8 +466,10 @@ hipError_t launch_sweep(const SysDev &S, const T *Phip, const double *prop, doub
 
 template <typename T>
 hipError_t configure_sweep(size_t lds) {
-    const void *f[4] = {(const void *)k_sweep_r<T, 16, false>, (const void *)k_sweep_r<T, 32, false>,
-                        (const void *)k_sweep_r<T, 48, false>, (const void *)k_sweep_r<T, 64, false>};
+    const void *f[8] = {(const void *)k_sweep_r<T, 16, false>, (const void *)k_sweep_r<T, 32, false>,
+                        (const void *)k_sweep_r<T, 48, false>, (const void *)k_sweep_r<T, 64, false>,
+                        (const void *)k_sweep_r<T, 16, true>,  (const void *)k_sweep_r<T, 32, true>,
+                        (const void *)k_sweep_r<T, 48, true>,  (const void *)k_sweep_r<T, 64, true>};
     for (const void *g : f) {
         const hipError_t e = hipFuncSetAttribute(g, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
