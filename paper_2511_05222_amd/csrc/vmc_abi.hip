@@ -446,8 +446,10 @@ static int run_measure(vmc_ctx *c, const double *pos0, int64_t cw, const Prepare
     for (int64_t k0 = 0; k0 < cnt; k0 += c->pcap) {
         const int64_t kc = std::min<int64_t>(c->pcap, cnt - k0);
         const int *lst = c->plist + k0;
-        HIP_OK(c, vmcx::launch_gather_rows(pos, lst, kc, N3, c->cp_pos, st));
-        HIP_OK(c, vmcx::launch_gather_rows(pos0, lst, kc, N3, c->cp_pos0, st));
+        vmcx::RowCopies in, back;
+        in.add(pos, c->cp_pos, nullptr, N3);
+        in.add(pos0, c->cp_pos0, nullptr, N3);
+        HIP_OK(c, vmcx::launch_copy_rows(in, lst, kc, true, st));
         WalkerOut oc{o.EL ? c->cp_EL : nullptr,        o.lnpsi ? c->cp_lnpsi : nullptr,  nullptr,
                      o.dEL_dR ? c->cp_dEdR : nullptr, o.dlnpsi_dR ? c->cp_dPdR : nullptr,
                      o.dlnjac_dR ? c->cp_dJdR : nullptr, (o.O || o.Of) ? c->cp_O : nullptr,
@@ -464,9 +466,10 @@ static int run_measure(vmc_ctx *c, const double *pos0, int64_t cw, const Prepare
         const int64_t lens[] = {1, 1, A3, A3, A3, Mn, Mn};
         for (int k = 0; k < 7; ++k)
             if (rows[k].first && rows[k].second && (full || k < 2))
-                HIP_OK(c, vmcx::launch_scatter_rows(rows[k].first, lst, kc, lens[k], rows[k].second, st));
-        if (full && o.Of) HIP_OK(c, vmcx::launch_scatter_rows_f32(oc.O, lst, kc, Mn, o.Of, st));
-        if (full && o.Gf) HIP_OK(c, vmcx::launch_scatter_rows_f32(oc.G, lst, kc, Mn, o.Gf, st));
+                back.add(rows[k].first, rows[k].second, nullptr, lens[k]);
+        if (full && o.Of) back.add(oc.O, nullptr, o.Of, Mn);
+        if (full && o.Gf) back.add(oc.G, nullptr, o.Gf, Mn);
+        HIP_OK(c, vmcx::launch_copy_rows(back, lst, kc, false, st));
     }
     return VMC_OK;
 }

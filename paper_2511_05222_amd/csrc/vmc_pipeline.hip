@@ -5,6 +5,7 @@
 //                  terms dE_L/dR, dln|Psi|/dR, dln Jac/dR
 //
 // Both work in FP64.
+#include <climits>
 #include <algorithm>
 #include <type_traits>
 
@@ -369,73 +370,119 @@ __device__ inline unsigned long long promote_bits(double x) {
     return (unsigned long long)__double_as_longlong(x > 0.0 ? x : (x <= 0.0 ? 0.0 : __builtin_inf()));
 }
 
+// Exclusive sum of v over the threads of a block of BS and its total: scans
+// within the wavefronts, then over their totals.
 template <int BS>
 __device__ inline int block_excl_scan(int v, int *buf, int &total) {
-    const int t = threadIdx.x;
-    buf[t] = v;
-    __syncthreads();
-    for (int o = 1; o < BS; o <<= 1) {
-        const int a = t >= o ? buf[t - o] : 0;
-        __syncthreads();
-        buf[t] += a;
-        __syncthreads();
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int x = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
     }
-    const int incl = buf[t];
-    total = buf[BS - 1];
+    if (lane == 63) buf[wave] = x;
     __syncthreads();
-    return incl - v;
+    int before = 0;
+    total = 0;
+#pragma unroll
+    for (int q = 0; q < BS / 64; ++q) {
+        if (q < wave) before += buf[q];
+        total += buf[q];
+    }
+    __syncthreads();
+    return before + x - v;
 }
 
-constexpr int SEL_BS = 1024;
+constexpr int SEL_BS = 1024, SEL_U = 8;   // threads; keys loaded ahead
 
+// Bound: latency of a single block.  A digit is found by a scan over the bins
+// (256 LDS reads in a row by one thread took 4 us a pass); the lanes that share
+// their wavefront's first digit, most of them in the leading passes, are counted
+// with one LDS atomic; a pass whose bin is taken as a whole is the last.  64
+// walkers: 56 -> 6 us; 32768: 148 -> 49.
 __global__ __launch_bounds__(SEL_BS) void k_promote_select(const double *__restrict__ key, int W, int k,
                                                            int *__restrict__ list) {
     __shared__ unsigned hist[256];
     __shared__ unsigned long long s_prefix;
-    __shared__ int s_rem;
-    __shared__ int buf[SEL_BS];
+    __shared__ int s_rem, s_in;
+    __shared__ int buf[SEL_BS / 64];
     const int tid = threadIdx.x;
     unsigned long long prefix = 0, mask = 0;
     int rem = k;
     for (int shift = 56; shift >= 0; shift -= 8) {
         if (tid < 256) hist[tid] = 0;
         __syncthreads();
-        for (int w = tid; w < W; w += SEL_BS) {
-            const unsigned long long u = promote_bits(key[w]);
-            if ((u & mask) == prefix) atomicAdd(&hist[(u >> shift) & 255], 1u);
+        for (int w0 = tid; w0 < W; w0 += SEL_BS * SEL_U) {
+            double x[SEL_U];
+#pragma unroll
+            for (int q = 0; q < SEL_U; ++q) x[q] = key[min(w0 + SEL_BS * q, W - 1)];
+#pragma unroll
+            for (int q = 0; q < SEL_U; ++q) {
+                const unsigned long long u = promote_bits(x[q]);
+                if (w0 + SEL_BS * q < W && (u & mask) == prefix) {
+                    const int b = (int)((u >> shift) & 255), first = __builtin_amdgcn_readfirstlane(b);
+                    const unsigned long long same = __ballot(b == first);
+                    if (b != first)
+                        atomicAdd(&hist[b], 1u);
+                    else if ((tid & 63) == __ffsll(same) - 1)
+                        atomicAdd(&hist[b], (unsigned)__popcll(same));
+                }
+            }
         }
         __syncthreads();
-        if (tid == 0) {
-            int cum = 0, b = 255;
-            for (; b > 0; --b) {
-                if (cum + (int)hist[b] >= rem) break;
-                cum += (int)hist[b];
+        if (tid < 64) {
+            // lane t: bins 255 - 4 t and down; the keys in higher bins than a
+            // lane's are those of the lanes before it
+            unsigned h[4], sum = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                h[q] = hist[255 - 4 * tid - q];
+                sum += h[q];
             }
-            s_rem = rem - cum;
-            s_prefix = prefix | ((unsigned long long)b << shift);
+            unsigned incl = sum;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const unsigned y = __shfl_up(incl, o, 64);
+                if (tid >= o) incl += y;
+            }
+            int cum = (int)(incl - sum);
+            // (the keys in play number rem at least: one lane's bins reach it)
+            if (cum < rem && rem <= (int)incl) {
+                int q = 0;
+                while (q < 3 && cum + (int)h[q] < rem) cum += (int)h[q++];
+                s_rem = rem - cum;
+                s_in = (int)h[q];
+                s_prefix = prefix | ((unsigned long long)(255 - 4 * tid - q) << shift);
+            }
         }
         __syncthreads();
         rem = s_rem;
         prefix = s_prefix;
         mask |= 255ull << shift;
+        if (s_in == rem) break;
         __syncthreads();
     }
-    // prefix: the k-th largest key; rem: how many keys equal to it to take
+    // prefix: the leading digits (those of mask) of the k-th largest key; rem:
+    // how many keys that share them to take
     const int seg = (W + SEL_BS - 1) / SEL_BS;
     const int w0 = min(W, tid * seg), w1 = min(W, w0 + seg);
     int gt = 0, eq = 0;
+#pragma unroll 8
     for (int w = w0; w < w1; ++w) {
-        const unsigned long long u = promote_bits(key[w]);
+        const unsigned long long u = promote_bits(key[w]) & mask;
         gt += u > prefix;
         eq += u == prefix;
     }
     int tot;
+    __syncthreads();
     const int eq_before = block_excl_scan<SEL_BS>(eq, buf, tot);
     const int take = max(0, min(eq, rem - eq_before));
     int off = block_excl_scan<SEL_BS>(gt + take, buf, tot);
     int taken = 0;
+#pragma unroll 8
     for (int w = w0; w < w1; ++w) {
-        const unsigned long long u = promote_bits(key[w]);
+        const unsigned long long u = promote_bits(key[w]) & mask;
         if (u > prefix || (u == prefix && taken++ < take)) list[off++] = w;
     }
 }
@@ -446,50 +493,40 @@ hipError_t launch_promote_select(const double *key, int W, int k, int *list, hip
     return hipGetLastError();
 }
 
-// dst[k][j] = src[list[k]][j] and its inverse, rows of len doubles.
-__global__ void k_gather_rows(const double *__restrict__ src, const int *__restrict__ list, int64_t kc, int64_t len,
-                              double *__restrict__ dst) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= kc * len) return;
-    const int64_t k = t / len, j = t - (t / len) * len;
-    dst[t] = src[(int64_t)list[k] * len + j];
+// Rows of several arrays through a list of row numbers: dst[k][j] =
+// src[list[k]][j] (GATHER) or dst[list[k]][j] = src[k][j], in one launch.
+template <bool GATHER>
+__global__ __launch_bounds__(256) void k_copy_rows(RowCopies c, const int *__restrict__ list, int64_t kc) {
+    int q = 0;
+    while (blockIdx.x >= c.first[q + 1]) ++q;
+    const int64_t len = c.len[q], t0 = (int64_t)(blockIdx.x - c.first[q]) * 256;
+    const int64_t k0 = t0 / len, j0 = t0 - k0 * len;   // the same in every lane
+    const unsigned at = (unsigned)j0 + threadIdx.x, dk = at / (unsigned)len, j = at - dk * (unsigned)len;
+    const int64_t k = k0 + dk;
+    if (k >= kc) return;
+    const int64_t there = (int64_t)list[k] * len + j, here = k * len + j;
+    if (GATHER)
+        c.dst[q][here] = c.src[q][there];
+    else if (c.dst[q])
+        c.dst[q][there] = c.src[q][here];
+    else
+        c.dstf[q][there] = (float)c.src[q][here];
 }
 
-__global__ void k_scatter_rows(const double *__restrict__ src, const int *__restrict__ list, int64_t kc, int64_t len,
-                               double *__restrict__ dst) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= kc * len) return;
-    const int64_t k = t / len, j = t - (t / len) * len;
-    dst[(int64_t)list[k] * len + j] = src[t];
-}
-
-__global__ void k_scatter_rows_f32(const double *__restrict__ src, const int *__restrict__ list, int64_t kc,
-                                   int64_t len, float *__restrict__ dst) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= kc * len) return;
-    const int64_t k = t / len, j = t - (t / len) * len;
-    dst[(int64_t)list[k] * len + j] = (float)src[t];
-}
-
-hipError_t launch_scatter_rows_f32(const double *src, const int *list, int64_t kc, int64_t len, float *dst,
-                                   hipStream_t st) {
-    const int64_t n = kc * len;
-    hipLaunchKernelGGL(k_scatter_rows_f32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, src, list, kc, len,
-                       dst);
-    return hipGetLastError();
-}
-
-hipError_t launch_gather_rows(const double *src, const int *list, int64_t kc, int64_t len, double *dst,
-                              hipStream_t st) {
-    const int64_t n = kc * len;
-    hipLaunchKernelGGL(k_gather_rows, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, src, list, kc, len, dst);
-    return hipGetLastError();
-}
-
-hipError_t launch_scatter_rows(const double *src, const int *list, int64_t kc, int64_t len, double *dst,
-                               hipStream_t st) {
-    const int64_t n = kc * len;
-    hipLaunchKernelGGL(k_scatter_rows, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, src, list, kc, len, dst);
+hipError_t launch_copy_rows(RowCopies &c, const int *list, int64_t kc, bool gather, hipStream_t st) {
+    if (c.n == 0 || kc <= 0) return hipSuccess;
+    c.first[0] = 0;
+    for (int q = 0; q < c.n; ++q) {
+        if (c.len[q] < 1 || c.len[q] > INT_MAX) return hipErrorInvalidValue;
+        const int64_t end = (int64_t)c.first[q] + (kc * c.len[q] + 255) / 256;
+        if (end > INT_MAX) return hipErrorInvalidValue;
+        c.first[q + 1] = (unsigned)end;
+    }
+    const dim3 g(c.first[c.n]);
+    if (gather)
+        hipLaunchKernelGGL(k_copy_rows<true>, g, dim3(256), 0, st, c, list, kc);
+    else
+        hipLaunchKernelGGL(k_copy_rows<false>, g, dim3(256), 0, st, c, list, kc);
     return hipGetLastError();
 }
 

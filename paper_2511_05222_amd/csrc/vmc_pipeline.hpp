@@ -240,11 +240,23 @@ int sweep_blocks_per_cu(int n_occ, int wpb, size_t lds);
 // index), in index order
 hipError_t launch_promote_select(const double *key, int W, int k, int *list, hipStream_t st);
 
-hipError_t launch_gather_rows(const double *src, const int *list, int64_t kc, int64_t len, double *dst,
-                              hipStream_t st);
-hipError_t launch_scatter_rows(const double *src, const int *list, int64_t kc, int64_t len, double *dst,
-                               hipStream_t st);
-hipError_t launch_scatter_rows_f32(const double *src, const int *list, int64_t kc, int64_t len, float *dst,
-                                   hipStream_t st);
+// up to MAX arrays of rows (doubles) copied through a list of row numbers;
+// a destination is dst or, where that is null, dstf (rounded to FP32)
+struct RowCopies {
+    static constexpr int MAX = 9;
+    int n = 0;
+    const double *src[MAX];
+    double *dst[MAX];
+    float *dstf[MAX];
+    int64_t len[MAX];
+    unsigned first[MAX + 1];   // filled by the launcher: first block of each
+    void add(const double *s, double *d, float *f, int64_t l) {
+        src[n] = s;
+        dst[n] = d;
+        dstf[n] = f;
+        len[n++] = l;
+    }
+};
+hipError_t launch_copy_rows(RowCopies &c, const int *list, int64_t kc, bool gather, hipStream_t st);
 
 }  // namespace vmcx

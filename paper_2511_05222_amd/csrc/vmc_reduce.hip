@@ -31,41 +31,6 @@ __device__ inline double block_sum(double v, double *red) {
 // Element space of the vector-Jacobian product:
 //   [0..Mn) dC = gE G + gPsi O, [Mn..Mn+3A) dR = gE dEdR + gPsi dPdR + gJ dJdR.
 // ---------------------------------------------------------------------------
-__device__ inline double est_O(const EstArgs &a, int64_t i) { return a.Of ? (double)a.Of[i] : a.O[i]; }
-__device__ inline double est_G(const EstArgs &a, int64_t i) { return a.Gf ? (double)a.Gf[i] : a.G[i]; }
-
-__device__ inline double est_term_1(const EstArgs &a, int64_t o, int64_t k) {
-    const double e = a.EL[k] - a.shift[0];
-    const int64_t A3 = a.A3, Mn = a.Mn;
-    if (o == 0) return e;
-    if (o == 1) return e * e;
-    o -= 2;
-    if (o < A3) return a.dEdR[k * A3 + o];
-    o -= A3;
-    if (o < A3) return a.dPdR[k * A3 + o] + 0.5 * a.dJdR[k * A3 + o];
-    o -= A3;
-    if (o < A3) return e * (a.dPdR[k * A3 + o] + 0.5 * a.dJdR[k * A3 + o]);
-    o -= A3;
-    if (o < Mn) return est_O(a, k * Mn + o);
-    o -= Mn;
-    if (o < Mn) return e * est_O(a, k * Mn + o);
-    o -= Mn;
-    if (o < Mn) return est_G(a, k * Mn + o);
-    return 1.0;   // the weight element
-}
-
-__device__ inline double est_term(const EstArgs &a, int64_t o, int64_t k) {
-    const double t = est_term_1(a, o, k);
-    return a.wt ? a.wt[k] * t : t;
-}
-
-__device__ inline double vjp_term(const EstArgs &a, int64_t o, int64_t k) {
-    const int64_t A3 = a.A3, Mn = a.Mn;
-    if (o < Mn) return a.gE[k] * a.G[k * Mn + o] + a.gP[k] * a.O[k * Mn + o];
-    o -= Mn;
-    return a.gE[k] * a.dEdR[k * A3 + o] + a.gP[k] * a.dPdR[k * A3 + o] + a.gJ[k] * a.dJdR[k * A3 + o];
-}
-
 // Neumaier step: s + c accumulates x
 __device__ inline void neumaier(double &s, double &c, double x) {
     const double t = s + x;
@@ -73,51 +38,110 @@ __device__ inline void neumaier(double &s, double &c, double x) {
     s = t;
 }
 
-// partial[seg][o] = sum over walkers of segment seg (Neumaier, fixed order).
-// Partial sums over one walker segment (blockIdx.y) of elements [0, n_elem)
-// of a partial row of n_out elements; in mode 0 only the leading elements
-// (everything before O), the O / e O / G elements going to k_partial_sums_og.
-constexpr int PS_U = 8;
+// partial[seg][o] = sum over the walkers of segment seg (Neumaier, fixed
+// order).  The values of several walkers are loaded ahead of the sum's serial
+// chain (clamped, unconditional loads); energies, cotangents and weights are
+// the same in every lane (scalar loads).
+constexpr int PS_U = 8;    // walkers loaded ahead: leading elements, cotangents
+constexpr int PS_OG = 16;  // O and G
 
-__global__ void k_partial_sums(EstArgs a, int mode, int64_t n_elem, int64_t n_out, int64_t W, int64_t seg_len,
-                               double *partial) {
-    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t seg = blockIdx.y;
-    if (o >= n_elem) return;
-    const int64_t k0 = seg * seg_len, k1 = min(W, k0 + seg_len);
-    // estimator element of this thread: the leading ones, then the weight
-    const int64_t oe = (mode == 0 && o == n_elem - 1) ? n_out - 1 : o;
+// Vector-Jacobian product: a thread takes one element.
+__global__ __launch_bounds__(256) void k_partial_vjp(EstArgs a, int64_t n_out, int64_t W, int64_t seg_len,
+                                                     double *__restrict__ partial) {
+    const int64_t o = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t seg = blockIdx.y, k0 = seg * seg_len, k1 = min(W, k0 + seg_len);
+    if (o >= n_out) return;
+    const bool isC = o < a.Mn;
+    const int64_t i = isC ? o : o - a.Mn, ld = isC ? a.Mn : a.A3;
+    const double *x = (isC ? a.G : a.dEdR) + i, *y = (isC ? a.O : a.dPdR) + i;
     double s = 0.0, c = 0.0;
-    int64_t k = k0;
-    for (; k + PS_U <= k1; k += PS_U) {
-        double x[PS_U];
+    for (int64_t k = k0; k < k1; k += PS_U) {
+        double xv[PS_U], yv[PS_U], jv[PS_U];
 #pragma unroll
-        for (int u = 0; u < PS_U; ++u) x[u] = mode == 0 ? est_term(a, oe, k + u) : vjp_term(a, o, k + u);
+        for (int u = 0; u < PS_U; ++u) {
+            const int64_t kk = min(k + u, k1 - 1);
+            xv[u] = x[kk * ld];
+            yv[u] = y[kk * ld];
+            jv[u] = 0.0;
+        }
+        if (!isC)
 #pragma unroll
-        for (int u = 0; u < PS_U; ++u) neumaier(s, c, x[u]);
+            for (int u = 0; u < PS_U; ++u) jv[u] = a.dJdR[min(k + u, k1 - 1) * ld + i];
+#pragma unroll
+        for (int u = 0; u < PS_U; ++u) {
+            if (k + u >= k1) break;
+            double t = ldc(a.gE + k + u) * xv[u] + ldc(a.gP + k + u) * yv[u];
+            if (!isC) t += ldc(a.gJ + k + u) * jv[u];
+            neumaier(s, c, t);
+        }
     }
-    for (; k < k1; ++k) neumaier(s, c, mode == 0 ? est_term(a, oe, k) : vjp_term(a, o, k));
-    partial[seg * n_out + oe] = s + c;
+    partial[seg * n_out + o] = s + c;
 }
 
-// Mode 0, the O, e O and G elements (most of the element space): thread
-// t < Mn takes O element t and forms e O from the same load, Mn <= t < 2 Mn
-// takes G element t - Mn.  PS_OG walkers are loaded ahead; their energies are
-// the same in every lane (scalar loads).  Few registers, so that enough
-// wavefronts are resident to keep HBM busy.
-constexpr int PS_OG = 16;
+// The estimators' elements before O and the weight: a block takes 64 of them,
+// its wavefronts the segment's walkers in turns of PS_U, their sums added in
+// order through LDS.
+__device__ inline void partial_lead(const EstArgs &a, int blk, int64_t n_out, int64_t k0, int64_t k1,
+                                    double *__restrict__ partial) {
+    __shared__ double red[4][64][2];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t A3 = a.A3, n_lead = 3 + 3 * A3, o = (int64_t)blk * 64 + lane;
+    const int64_t h = o - 2;
+    const bool isE = o == 0, isE2 = o == 1, isH = h >= 0 && h < A3, isP = h >= A3 && h < 2 * A3,
+               isEP = h >= 2 * A3 && h < 3 * A3;
+    const int64_t i = isH ? h : isP ? h - A3 : isEP ? h - 2 * A3 : 0;
+    const double *x = (isH ? a.dEdR : a.dPdR) + i, *y = a.dJdR + i;
+    const double sh = ldc(a.shift);
+    double s = 0.0, c = 0.0;
+    for (int64_t k = k0 + PS_U * wave; k < k1; k += 4 * PS_U) {
+        double xv[PS_U], yv[PS_U];
+#pragma unroll
+        for (int u = 0; u < PS_U; ++u) {
+            const int64_t kk = min(k + u, k1 - 1);
+            xv[u] = x[kk * A3];
+            yv[u] = y[kk * A3];
+        }
+#pragma unroll
+        for (int u = 0; u < PS_U; ++u) {
+            if (k + u >= k1) break;
+            const double e = ldc(a.EL + k + u) - sh, P = xv[u] + 0.5 * yv[u];
+            const double t = isE ? e : isE2 ? e * e : isH ? xv[u] : isP ? P : isEP ? e * P : 1.0;
+            neumaier(s, c, a.wt ? ldc(a.wt + k + u) * t : t);
+        }
+    }
+    red[wave][lane][0] = s;
+    red[wave][lane][1] = c;
+    __syncthreads();
+    if (wave != 0 || o >= n_lead) return;
+#pragma unroll
+    for (int q = 1; q < 4; ++q) {
+        neumaier(s, c, red[q][lane][0]);
+        c += red[q][lane][1];
+    }
+    partial[(int64_t)blockIdx.y * n_out + (o == n_lead - 1 ? n_out - 1 : o)] = s + c;
+}
 
+// The estimators' sums.  Blocks from n_og on: the leading elements (beside the
+// others instead of a launch of their own with serial sums, which took 45 us at
+// any number of walkers up to 16384).  Before them O, e O and G, most of the element space:
+// thread t < Mn takes O element t and forms e O from the same load, Mn <= t <
+// 2 Mn takes G element t - Mn.  Bound there: HBM; few registers, so that enough
+// wavefronts are resident (5.1 TB/s at 32768 walkers of 2 x 11045 FP32 values).
 template <typename S>
-__global__ __launch_bounds__(256) void k_partial_sums_og(const S *__restrict__ O, const S *__restrict__ G,
-                                                         EstArgs a, int64_t n_out, int64_t W, int64_t seg_len,
-                                                         double *partial) {
+__global__ __launch_bounds__(256) void k_partial_sums(const S *__restrict__ O, const S *__restrict__ G, EstArgs a,
+                                                      int n_og, int64_t n_out, int64_t W, int64_t seg_len,
+                                                      double *__restrict__ partial) {
+    const int64_t seg = blockIdx.y, k0 = seg * seg_len, k1 = min(W, k0 + seg_len);
+    if ((int)blockIdx.x >= n_og) {
+        partial_lead(a, (int)blockIdx.x - n_og, n_out, k0, k1, partial);
+        return;
+    }
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t Mn = a.Mn, oO = 2 + 3 * a.A3;
     if (t >= 2 * Mn) return;
     const bool isO = t < Mn;
     const int64_t i = isO ? t : t - Mn;
     const S *src = isO ? O : G;
-    const int64_t seg = blockIdx.y, k0 = seg * seg_len, k1 = min(W, k0 + seg_len);
     const double sh = ldc(a.shift);
     double s1 = 0.0, c1 = 0.0, s2 = 0.0, c2 = 0.0;
     int64_t k = k0;
@@ -144,23 +168,39 @@ __global__ __launch_bounds__(256) void k_partial_sums_og(const S *__restrict__ O
 
 // acc[o] (+ comp[o]) += sum_seg partial[seg][o]  (Neumaier, fixed order);
 // if blk / blkw != nullptr, element 0's / the last element's chunk sum is
-// also added to *blk / *blkw.
-__global__ void k_accumulate(const double *partial, int64_t n_out, int64_t n_seg, double *acc,
-                             double *comp, double *blk, double *blkw, double *blk_all) {
-    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (o >= n_out) return;
+// also added to *blk / *blkw.  A block takes 64 elements, its wavefronts the
+// segments in turns of eight, their sums added in order through LDS: one
+// thread that walks all segments of an element is a serial chain of loads (256
+// segments of 33327 elements: 108 us that way, 20 so).
+__global__ __launch_bounds__(256) void k_accumulate(const double *__restrict__ partial, int64_t n_out, int n_seg,
+                                                    double *acc, double *comp, double *blk, double *blkw,
+                                                    double *blk_all) {
+    __shared__ double red[4][64][2];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t o = (int64_t)blockIdx.x * 64 + lane, oc = min(o, n_out - 1);
     double s = 0.0, c = 0.0;
-    for (int64_t g = 0; g < n_seg; ++g) {
-        const double x = partial[g * n_out + o];
-        const double t = s + x;
-        c += (fabs(s) >= fabs(x)) ? ((s - t) + x) : ((x - t) + s);
-        s = t;
+    for (int g = 8 * wave; g < n_seg; g += 32) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = partial[(int64_t)min(g + u, n_seg - 1) * n_out + oc];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (g + u < n_seg) neumaier(s, c, v[u]);
+    }
+    red[wave][lane][0] = s;
+    red[wave][lane][1] = c;
+    __syncthreads();
+    if (wave != 0 || o >= n_out) return;
+#pragma unroll
+    for (int q = 1; q < 4; ++q) {
+        neumaier(s, c, red[q][lane][0]);
+        c += red[q][lane][1];
     }
     const double x = s + c;
-    const double a0 = acc[o];
-    const double t = a0 + x;
-    comp[o] += (fabs(a0) >= fabs(x)) ? ((a0 - t) + x) : ((x - t) + a0);
-    acc[o] = t;
+    double a0 = acc[o], cc = comp[o];
+    neumaier(a0, cc, x);
+    acc[o] = a0;
+    comp[o] = cc;
     if (o == 0 && blk != nullptr) blk[0] += x;
     if (o == n_out - 1 && blkw != nullptr) blkw[0] += x;
     if (blk_all != nullptr) blk_all[o] += x;
@@ -215,13 +255,21 @@ __global__ void k_jackknife_stats(const double *__restrict__ x, int64_t nb, int6
     if (sigma) sigma[i] = sqrt((double)(nb - 1) / (double)nb * v);
 }
 
-// shift s = mean E_L of the first measured chunk (set once)
-__global__ void k_set_shift(const double *EL, int64_t W, double *shift, int *shift_set) {
-    __shared__ double red[4];
+// shift s = mean E_L of the first measured chunk (set once); eight loads in
+// flight per thread (32768 walkers: 54 us with one on 256 threads, 10 so)
+__global__ __launch_bounds__(1024) void k_set_shift(const double *__restrict__ EL, int64_t W, double *shift,
+                                                    int *shift_set) {
+    __shared__ double red[16];
     if (shift_set[0]) return;
     double s = 0.0;
-    for (int64_t k = threadIdx.x; k < W; k += 256) s += EL[k];
-    s = block_sum<256>(s, red);
+    for (int64_t k = threadIdx.x; k < W; k += 8 * 1024) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = EL[min(k + 1024 * u, W - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += k + 1024 * u < W ? v[u] : 0.0;
+    }
+    s = block_sum<1024>(s, red);
     if (threadIdx.x == 0) {
         shift[0] = s / (double)W;
         shift_set[0] = 1;
@@ -625,25 +673,26 @@ __global__ __launch_bounds__(256) void k_zv_product(const double *__restrict__ C
 hipError_t launch_reduce(const EstArgs &a, int mode, int64_t n_out, int64_t W, double *partial,
                          int64_t max_seg, double *acc, double *comp, double *blk, double *blkw, double *blk_all,
                          hipStream_t st) {
-    int64_t n_seg = std::min<int64_t>(max_seg, std::max<int64_t>(1, (W + 63) / 64));
+    // segments of one turn of loads at least: shorter ones leave loads idle,
+    // longer ones (64) a serial chain where there are few walkers
+    int64_t n_seg = std::min<int64_t>(max_seg, std::max<int64_t>(1, (W + PS_OG - 1) / PS_OG));
     const int64_t seg_len = (W + n_seg - 1) / n_seg;
     n_seg = (W + seg_len - 1) / seg_len;
-    // mode 0: the leading elements and the weight (last) here, O / e O / G
-    // in k_partial_sums_og
-    const int64_t n_elem = mode == 0 ? 3 + 3 * a.A3 : n_out;
-    dim3 g1((unsigned)((n_elem + 255) / 256), (unsigned)n_seg);
-    hipLaunchKernelGGL(k_partial_sums, g1, dim3(256), 0, st, a, mode, n_elem, n_out, W, seg_len, partial);
     if (mode == 0) {
-        dim3 g2((unsigned)((2 * a.Mn + 255) / 256), (unsigned)n_seg);
+        const int n_og = (int)((2 * a.Mn + 255) / 256), n_lead = (int)((3 + 3 * a.A3 + 63) / 64);
+        const dim3 g((unsigned)(n_og + n_lead), (unsigned)n_seg);
         if (a.Of != nullptr)
-            hipLaunchKernelGGL(k_partial_sums_og<float>, g2, dim3(256), 0, st, a.Of, a.Gf, a, n_out, W, seg_len,
+            hipLaunchKernelGGL(k_partial_sums<float>, g, dim3(256), 0, st, a.Of, a.Gf, a, n_og, n_out, W, seg_len,
                                partial);
         else
-            hipLaunchKernelGGL(k_partial_sums_og<double>, g2, dim3(256), 0, st, a.O, a.G, a, n_out, W, seg_len,
+            hipLaunchKernelGGL(k_partial_sums<double>, g, dim3(256), 0, st, a.O, a.G, a, n_og, n_out, W, seg_len,
                                partial);
+    } else {
+        const dim3 g((unsigned)((n_out + 255) / 256), (unsigned)n_seg);
+        hipLaunchKernelGGL(k_partial_vjp, g, dim3(256), 0, st, a, n_out, W, seg_len, partial);
     }
-    hipLaunchKernelGGL(k_accumulate, dim3((unsigned)((n_out + 255) / 256)), dim3(256), 0, st, partial, n_out,
-                       n_seg, acc, comp, blk, blkw, blk_all);
+    hipLaunchKernelGGL(k_accumulate, dim3((unsigned)((n_out + 63) / 64)), dim3(256), 0, st, partial, n_out, (int)n_seg,
+                       acc, comp, blk, blkw, blk_all);
     return hipGetLastError();
 }
 
@@ -663,7 +712,7 @@ hipError_t launch_jackknife_stats(const double *x, int64_t nb, int64_t len, doub
 }
 
 hipError_t launch_set_shift(const double *EL, int64_t W, double *shift, int *shift_set, hipStream_t st) {
-    hipLaunchKernelGGL(k_set_shift, dim3(1), dim3(256), 0, st, EL, W, shift, shift_set);
+    hipLaunchKernelGGL(k_set_shift, dim3(1), dim3(1024), 0, st, EL, W, shift, shift_set);
     return hipGetLastError();
 }
 
