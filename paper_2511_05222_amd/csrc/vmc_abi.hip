@@ -268,13 +268,26 @@ static AdjLayout adjoint_layout(const vmc_ctx *c, size_t ts) {
     a.off_a = kb;
     a.off_p = 2 * kb;
     a.off_g = a.off_p + al((size_t)3 * N * 8);
-    a.off_d = a.off_g + al((size_t)3 * N * 8);
-    // FP32 needs about 140 registers (three wavefronts per SIMD): blocks of
+    a.off_d = a.off_g + al((size_t)3 * N * ts);
+    // FP32 needs about 160 registers (three wavefronts per SIMD): blocks of
     // four wavefronts let three walkers share a CU; FP64 (about 250) runs two
-    // per SIMD, one block of eight
-    a.waves = ts == sizeof(float) ? 4 : 8;
-    while (a.waves > 1 && (size_t)a.off_d + (size_t)a.waves * 3 * N * 8 > 160 * 1024) a.waves /= 2;
-    a.bytes = (size_t)a.off_d + (size_t)a.waves * 3 * N * 8;
+    // per SIMD: blocks of four where two fit, else one of eight.  (Blocks of
+    // five, one sub-tile each of a 75-AO molecule, double the load of one of
+    // the SIMDs: FP32 703 us, blocks of four 333.)  Per wavefront: dE_L/dr
+    // partials and, FP64, the radial sums that a sub-tile's AOs share.  Where
+    // those do not fit beside the rest (from 114 electrons) every AO's lane
+    // forms its own: fewer wavefronts would cost more than sharing saves.
+    const size_t max_lds = 160 * 1024, dw = al((size_t)3 * N * 8), xr = 8 * vmcx::ADJ_XS * 4 * ts;
+    auto lds = [&](int waves) { return a.off_d + waves * (dw + (a.shared ? xr : 0)); };
+    auto fit = [&](int waves) {
+        while (waves > 1 && lds(waves) > max_lds) waves /= 2;
+        return waves;
+    };
+    const int most = fit(8);
+    a.shared = ts == sizeof(double);
+    a.shared = a.shared && (nt < 4 || lds(most) <= max_lds);
+    a.waves = std::min(ts == sizeof(float) || 2 * lds(4) <= max_lds ? std::min(4, most) : fit(8), (c->M + 15) / 16);
+    a.bytes = lds(a.waves);
     return a;
 }
 

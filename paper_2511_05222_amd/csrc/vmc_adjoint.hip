@@ -15,28 +15,168 @@
 // whose B operand (K~, Abar rows e) comes from LDS.  Per AO the electron sums
 // of t_k and s_k go to tao; per electron the AO sums of t_k (dE_L/dr_e, the
 // determinant part) go to dedr_part, in a fixed order.
+//
+// Bound: issue (the matrix cores and the vector units of a SIMD take turns):
+// of the cycles of a row tile at 47 orbitals, FP32, 37 % are products and 44 %
+// the evaluations; FP64 34 % and 41 %, the rest latency that two wavefronts a
+// SIMD do not hide.
+//   FP64: an AO's lane used to form its shell's radial sums itself, each
+// shell's 2.3 times over with exponents read from memory; now eight lanes a
+// shell form them once (SHARED), in LDS until the AOs' lanes read them.  With
+// shorter algebra for t_k and one LDS update per sum (below): 235 AOs, 94
+// electrons, 16384 walkers 7.71 -> 6.93 ms, 75 AOs, 26 electrons 1.17 -> 0.66
+// (there also from four wavefronts a block for 5 sub-tiles), H2 30 -> 11 us.
+//   FP32: radial sums are cheap and in registers; shared they cost more in
+// LDS round trips than they save (6.50 against 6.08 ms, 235 AOs, 32768
+// walkers).
 #include "vmc_pipeline.hpp"
 #include "vmc_mfma.hpp"
+#include "vmc_regs.hpp"
 
 namespace vmcx {
 
-template <typename T, int NT>
-__global__ __launch_bounds__(512) void k_adjoint_mfma(SysDev S, const T *__restrict__ C,
-                                                      const double *__restrict__ R, MeasBufs<T> mb, WalkerOut out,
-                                                      AdjLayout L) {
+// The shell of one lane of the radial phase.
+template <typename T>
+struct ShellLane {
+    static constexpr int NP = 3;   // primitives held in registers
+    double x, y, z, alt[NP];       // alt = al log2(e) (FP32 exponential)
+    T al[NP], cp[NP];
+    int np, p0;
+};
+
+template <typename T>
+__device__ inline void shell_lane_load(const SysDev &S, const double *R, int s, ShellLane<T> &L) {
+    const int a = S.basis.shell_atom[s];
+    L.x = R[3 * a];
+    L.y = R[3 * a + 1];
+    L.z = R[3 * a + 2];
+    L.np = S.basis.shell_np[s];
+    L.p0 = S.basis.shell_p0[s];
+#pragma unroll
+    for (int k = 0; k < ShellLane<T>::NP; ++k) {
+        const int p = L.p0 + max(min(k, L.np - 1), 0);
+        L.al[k] = (T)S.basis.prim_exp[p];
+        L.cp[k] = k < L.np ? (T)S.basis.prim_cp[p] : T(0);   // padded primitives carry cp = 0
+        L.alt[k] = (double)L.al[k] * 1.4426950408889634;
+    }
+}
+
+// R0, u1, u2, u3 of ao_lane_radial for the lane's shell.
+template <typename T>
+__device__ inline void shell_lane_radial(const ShellLane<T> &L, const BasisDev &B, double rho, T *o) {
+    T r0 = T(0), r1 = T(0), r2 = T(0), r3 = T(0);
+    auto add = [&](T al, double alt, T cp) {
+        const T e = cp * prim_exp_neg<T>(al, alt, rho), al2 = al * al, al3 = al2 * al;
+        r0 += e;
+        r1 = fma(-al, e, r1);
+        r2 = fma(al2, e, r2);
+        r3 = fma(-al3, e, r3);
+    };
+#pragma unroll
+    for (int k = 0; k < ShellLane<T>::NP; ++k) add(L.al[k], L.alt[k], L.cp[k]);
+    for (int k = ShellLane<T>::NP; k < L.np; ++k) {
+        const T al = (T)B.prim_exp[L.p0 + k];
+        add(al, (double)al * 1.4426950408889634, (T)B.prim_cp[L.p0 + k]);
+    }
+    o[0] = r0;
+    o[1] = T(2) * r1;
+    o[2] = T(4) * r2;
+    o[3] = T(8) * r3;
+}
+
+// The lane's monomial P = eta x^a y^b z^c at (x, y, z): its gradient, its
+// Hessian times g and its Laplacian.
+template <typename T, int NPR>
+__device__ inline void ao_lane_monomial(const AoLane<T, NPR> &L, T x, T y, T z, T gx, T gy, T gz, T &P, T *dP,
+                                        T *HPg, T &lapP) {
+    const T r[3] = {x, y, z};
+    T f[3], f1[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const T h = fma(L.c2[q], r[q], L.c1[q]);
+        f[q] = fma(h, r[q], L.c0[q]);
+        f1[q] = fma(L.c2[q], r[q], h);
+    }
+    const T fyz = f[1] * f[2], fxz = f[0] * f[2], fxy = f[0] * f[1];
+    P = f[0] * fyz;
+    dP[0] = f1[0] * fyz;
+    dP[1] = f1[1] * fxz;
+    dP[2] = f1[2] * fxy;
+    const T Pxx = L.c22[0] * fyz, Pyy = L.c22[1] * fxz, Pzz = L.c22[2] * fxy;
+    const T Pxy = f1[0] * f1[1] * f[2], Pxz = f1[0] * f1[2] * f[1], Pyz = f1[1] * f1[2] * f[0];
+    lapP = Pxx + Pyy + Pzz;
+    HPg[0] = fma(Pxx, gx, fma(Pxy, gy, Pxz * gz));
+    HPg[1] = fma(Pxy, gx, fma(Pyy, gy, Pyz * gz));
+    HPg[2] = fma(Pxz, gx, fma(Pyz, gy, Pzz * gz));
+}
+
+// keep + the partner's send, the partner being lane ^ K of the DPP row
+template <int K>
+__device__ inline int row_xor(int v) {
+    if (K == 1) return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);   // quad_perm [1, 0, 3, 2]
+    if (K == 2) return __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);   // quad_perm [2, 3, 0, 1]
+    if (K == 8) return __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true);  // row_ror 8
+    // lanes 0-3 and 8-11 of the row from 4 above, the others from 4 below
+    const int up = __builtin_amdgcn_update_dpp(0, v, 0x104, 0xF, 0x5, true);
+    return __builtin_amdgcn_update_dpp(up, v, 0x114, 0xF, 0xA, true);
+}
+template <int K>
+__device__ inline float add_xor(float keep, float send) {
+    return keep + __int_as_float(row_xor<K>(__float_as_int(send)));
+}
+template <int K>
+__device__ inline double add_xor(double keep, double send) {
+    const long long b = __double_as_longlong(send);
+    const int lo = row_xor<K>((int)b), hi = row_xor<K>((int)(b >> 32));
+    return keep + __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
+// Sums of 3 or 6 values over the 16 lanes of a DPP row, one value a lane, by
+// halving what a lane holds at each step: lane m (of the row) returns the value
+// row16_which<NV>(m).  The pairs added are those of row16_sum_last (neighbours,
+// then twos, fours, eights).
+template <int NV>
+__device__ inline int row16_which(int m) {
+    return NV == 3 ? ((m & 2) ? 2 : (m & 1)) : ((m & 4) ? 4 : (m & 2)) + (m & 1);
+}
+template <typename T>
+__device__ inline T row16_sums(const T (&t)[3], int m) {
+    const T q0 = add_xor<1>((m & 1) ? t[1] : t[0], (m & 1) ? t[0] : t[1]), q1 = add_xor<1>(t[2], t[2]);
+    T u = add_xor<2>((m & 2) ? q1 : q0, (m & 2) ? q0 : q1);
+    u = add_xor<4>(u, u);
+    return add_xor<8>(u, u);
+}
+template <typename T>
+__device__ inline T row16_sums(const T (&t)[6], int m) {
+    T q[3], s[2];
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+        q[p] = add_xor<1>((m & 1) ? t[2 * p + 1] : t[2 * p], (m & 1) ? t[2 * p] : t[2 * p + 1]);
+    s[0] = add_xor<2>((m & 2) ? q[1] : q[0], (m & 2) ? q[0] : q[1]);
+    s[1] = add_xor<2>(q[2], q[2]);
+    const T u = add_xor<4>((m & 4) ? s[1] : s[0], (m & 4) ? s[0] : s[1]);
+    return add_xor<8>(u, u);
+}
+
+template <typename T, int NT, bool SHARED>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (NT == 1 ? 4 : 3) : 2)))
+void k_adjoint_mfma(SysDev S, const T *__restrict__ C, const double *__restrict__ R, MeasBufs<T> mb, WalkerOut out,
+                    AdjLayout L) {
     typedef Mfma<T> MF;
     constexpr int KS = 4 * NT;        // k-steps over orbitals (4 per step)
-    constexpr int NPR = sizeof(T) == 4 ? 3 : 0;   // primitives held in registers (FP32)
+    constexpr int NPR = SHARED ? 0 : (sizeof(T) == 4 ? 3 : 0);   // primitives an AO's lane holds
+    typedef T V4 __attribute__((ext_vector_type(4), aligned(16)));
     extern __shared__ __align__(16) unsigned char smem[];
     const int w = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
     const int N = S.N, n = S.n_occ, M = S.M;
     const int ldk = L.ldk, RT = L.rt;
     T *Ks = (T *)(smem + L.off_k);    // [RT*16][ldk]  K~[e][i]
     T *As = (T *)(smem + L.off_a);    // [RT*16][ldk]  Abar[e][i]
     double *sp = (double *)(smem + L.off_p);    // [N][3]
     T *sg = (T *)(smem + L.off_g);              // [N][3] Jastrow gradient (arithmetic type)
-    double *dpw = (double *)(smem + L.off_d);   // [nw][N][3] per-wave dE_L/dr_e partials
+    double *dpw = (double *)(smem + L.off_d);   // [nw][dst] per-wave dE_L/dr_e partials [N][3]
+    const int dst = (3 * N + 1) & ~1;
     const T *ktw = mb.ktil + (size_t)w * N * n;
     const T *abw = mb.abar + (size_t)w * N * n;
     // K~ and Abar into LDS, eight elements per thread in flight (clamped,
@@ -65,20 +205,38 @@ __global__ __launch_bounds__(512) void k_adjoint_mfma(SysDev S, const T *__restr
         sp[k] = mb.pos[(size_t)w * N * 3 + k];
         sg[k] = (T)mb.gb[(size_t)w * N * 6 + 6 * (k / 3) + (k - (k / 3) * 3)];
     }
-    for (int k = tid; k < nw * 3 * N; k += blockDim.x) dpw[k] = 0.0;
+    for (int k = tid; k < nw * dst; k += blockDim.x) dpw[k] = 0.0;
     __syncthreads();
-    double *dw = dpw + (size_t)wave * 3 * N;
+    // One block of eight wavefronts a CU: the wavefronts left without a last
+    // sub-tile differ from block to block (2.5 % at 15 sub-tiles; smaller
+    // blocks, several a CU, lose by it).  The partials are kept by share: the
+    // order of their sum is the same in every block.
+    const int share = nw == 8 ? (wave + (w >> 3) + (w >> 8)) & 7 : wave;
+    double *dw = dpw + share * dst;
+    V4 *xr = (V4 *)(dpw + nw * dst) + wave * 8 * ADJ_XS;   // radial sums, [8 electrons][ADJ_XS shells]
     const int ml = lane & 15, kg = lane >> 4;
+    // evaluations a turn, and the dE_L/dr sum this lane gets of a turn's
+    // (two where the registers allow it: fewer lane moves a sum)
+    constexpr int VU = sizeof(T) == 8 || NT == 3 ? 2 : 1;
+    const int dq = row16_which<3 * VU>(ml), de = MF::row(lane, dq / 3), dc = dq % 3;
+    const bool dmine = VU == 2 ? (ml & 8) == 0 && (ml & 6) != 6 : ml < 3;
+    // the electron (of 8) and shell of this lane in the radial phase
+    const int ri = lane & 7, rj = lane >> 3, re = MF::row(16 * (ri >> 1), ri & 1);
     const int n_sub = (M + 15) >> 4;
-    for (int st = wave; st < n_sub; st += nw) {
+    for (int st = share; st < n_sub; st += nw) {
         const int mu = 16 * st + ml;
         const bool vm = mu < M;
-        // this lane's AO: monomial and primitives in registers for the sub-tile
+        // this lane's AO: monomial (and primitives) in registers for the sub-tile
         AoLane<T, NPR> al;
         ao_lane_load<T, NPR>(S.basis, vm ? mu : M - 1, al);
         if (!vm) al.c0[0] = al.c1[0] = al.c2[0] = al.c22[0] = T(0);   // no AO: every component 0
-        const int atom = S.basis.shell_atom[S.basis.ao_shell[vm ? mu : M - 1]];
+        const int shell = S.basis.ao_shell[vm ? mu : M - 1], atom = S.basis.shell_atom[shell];
         const double Rx = R[3 * atom], Ry = R[3 * atom + 1], Rz = R[3 * atom + 2];
+        // the sub-tile's shells, this lane's AO's among them
+        const int s0 = ldc(S.basis.ao_shell + 16 * st), ns = ldc(S.basis.ao_shell + min(16 * st + 15, M - 1)) - s0 + 1;
+        const int sj = shell - s0;
+        ShellLane<T> sl;
+        if (SHARED) shell_lane_load<T>(S, R, s0 + min(rj, ns - 1), sl);
         T cB[KS];
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -100,50 +258,104 @@ __global__ __launch_bounds__(512) void k_adjoint_mfma(SysDev S, const T *__restr
                 kap = MF::fma(kr[4 * ks], cB[ks], kap);
                 aa = MF::fma(ar[4 * ks], cB[ks], aa);
             }
-            // one (e, mu) evaluation at a time: unrolled, four would be live.
-            // Every lane evaluates: past the last AO all components are 0,
-            // past the last electron (position of electron N - 1) kappa, a
-            // and the K~ / Abar rows are 0, so nothing of it reaches a sum.
+            // One evaluation (e, mu) at a time (interleaved, several would be
+            // live).  Every lane evaluates: past the last AO all
+            // components are 0, past the last electron (position of electron
+            // N - 1) kappa, a and the K~ / Abar rows are 0, so nothing of it
+            // reaches a sum.
 #pragma unroll 1
-            for (int v = 0; v < 4; ++v) {
-                const int e = 16 * rt + MF::row(lane, v), ec = min(e, N - 1);
-                const double dx = sp[3 * ec] - Rx, dy = sp[3 * ec + 1] - Ry, dz = sp[3 * ec + 2] - Rz;
-                const double rho_d = dx * dx + dy * dy + dz * dz;
-                const T x = (T)dx, y = (T)dy, z = (T)dz, rho = (T)rho_d;
-                T R0, u1, u2, u3;
-                ao_lane_radial<T, NPR>(al, S.basis, rho_d, R0, u1, u2, u3);
-                T d[14];
-                ao_lane_components<T, NPR>(al, x, y, z, rho, R0, u1, u2, u3, d);
-                const T gx = sg[3 * ec], gy = sg[3 * ec + 1], gz = sg[3 * ec + 2];
-                const T hgx = gx * d[5] + gy * d[6] + gz * d[7];
-                const T hgy = gx * d[6] + gy * d[8] + gz * d[9];
-                const T hgz = gx * d[7] + gy * d[9] + gz * d[10];
-                const T half = T(0.5);
-                const T kv = kap[v], av = aa[v];
-                const T t6[6] = {av * d[1] - kv * (hgx + half * d[11]), av * d[2] - kv * (hgy + half * d[12]),
-                                 av * d[3] - kv * (hgz + half * d[13]), kv * d[1], kv * d[2], kv * d[3]};
-                const T psi = d[0];
-                const T q = -(gx * d[1] + gy * d[2] + gz * d[3]) - half * d[4];
-#pragma unroll
-                for (int c = 0; c < 6; ++c) tl[c] += t6[c];
-                // AO sum of t_k for electron e over the 16 lanes of this row
-                // group (a DPP row), left in its last lane
-                const double d0 = (double)row16_sum_last<T>(t6[0]), d1 = (double)row16_sum_last<T>(t6[1]),
-                             d2 = (double)row16_sum_last<T>(t6[2]);
-                if (ml == 15 && e < N) {
-                    dw[3 * e] += d0;
-                    dw[3 * e + 1] += d1;
-                    dw[3 * e + 2] += d2;
+            for (int h = 0; h < 4; h += VU) {
+                V4 rs[2];
+                if (SHARED) {
+                    // radial sums of the sub-tile's shells, ADJ_XS at a time, at
+                    // the turn's 8 electrons, then to the lanes of their AOs
+                    const int ec = min(16 * rt + MF::row(0, h) + re, N - 1);
+                    const double px = sp[3 * ec], py = sp[3 * ec + 1], pz = sp[3 * ec + 2];
+                    for (int q = 0; q < ns; q += ADJ_XS) {
+                        if (ns > ADJ_XS) shell_lane_load<T>(S, R, s0 + min(q + rj, ns - 1), sl);
+                        const double dx = px - sl.x, dy = py - sl.y, dz = pz - sl.z;
+                        T o[4];
+                        shell_lane_radial<T>(sl, S.basis, dx * dx + dy * dy + dz * dz, o);
+                        wave_sync_s();
+                        if (rj < ADJ_XS) xr[ADJ_XS * ri + rj] = V4{o[0], o[1], o[2], o[3]};
+                        wave_sync_s();
+                        const int j = max(0, min(sj - q, ADJ_XS - 1));
+                        const V4 r0 = xr[2 * ADJ_XS * kg + j], r1 = xr[2 * ADJ_XS * kg + ADJ_XS + j];
+                        if (sj >= q) rs[0] = r0, rs[1] = r1;
+                    }
                 }
-                const T *kb = Ks + e * ldk + ml;
-                const T *ab = As + e * ldk + ml;
+                T t[3 * VU];
 #pragma unroll
-                for (int it = 0; it < NT; ++it) {
-                    const T bk = kb[16 * it], ba = ab[16 * it];
-                    accO[it] = MF::fma(psi, bk, accO[it]);
-                    accG[it] = MF::fma(psi, ba, accG[it]);
-                    accG[it] = MF::fma(q, bk, accG[it]);
+                for (int v = 0; v < VU; ++v) {
+                    const int e = 16 * rt + MF::row(lane, h) + MF::row(0, v), ec = min(e, N - 1);
+                    const double dx = sp[3 * ec] - Rx, dy = sp[3 * ec + 1] - Ry, dz = sp[3 * ec + 2] - Rz;
+                    const double rho_d = dx * dx + dy * dy + dz * dz;
+                    const T x = (T)dx, y = (T)dy, z = (T)dz, rho = (T)rho_d;
+                    T R0, u1, u2, u3;
+                    if (SHARED) {
+                        R0 = rs[v][0], u1 = rs[v][1], u2 = rs[v][2], u3 = rs[v][3];
+                    } else {
+                        ao_lane_radial<T, NPR>(al, S.basis, rho_d, R0, u1, u2, u3);
+                    }
+                    const T gx = sg[3 * ec], gy = sg[3 * ec + 1], gz = sg[3 * ec + 2];
+                    const T kv = kap[v], av = aa[v], half = T(0.5);
+                    T psi, q;
+                    if constexpr (sizeof(T) == 8) {
+                        // (95 FP64 operations where the 14 components and their
+                        // products with g take 125)
+                        T P, dP[3], HPg[3], lapP;
+                        ao_lane_monomial<T, NPR>(al, x, y, z, gx, gy, gz, P, dP, HPg, lapP);
+                        const T PR1 = P * u1, PR2 = P * u2, kR = kv * R0, kP = kv * PR1;
+                        const T xg = fma(x, gx, fma(y, gy, z * gz)), Pg = fma(dP[0], gx, fma(dP[1], gy, dP[2] * gz));
+                        // d_k psi = dP_k R + x_k 2 P R'
+                        // (H g)_k = (HP g)_k R + dP_k xg 2 R' + x_k (Pg 2 R' + xg 4 P R'') + g_k 2 P R'
+                        // d_k lap psi = x_k S1 + dP_k S2
+                        const T A = fma(Pg, u1, xg * PR2);
+                        const T S1 = fma(lapP, u1, fma(al.h820, PR2, rho * P * u3)), S2 = fma(al.h46, u1, rho * u2);
+                        const T cP = fma(av, R0, -kv * fma(xg, u1, half * S2)), cD = fma(av, PR1, -kv * fma(half, S1, A));
+                        const T r[3] = {x, y, z}, g[3] = {gx, gy, gz};
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) {
+                            const T tk = fma(cP, dP[c], fma(cD, r[c], -fma(kR, HPg[c], kP * g[c])));
+                            t[3 * v + c] = tk;
+                            tl[c] += tk;
+                            tl[3 + c] = fma(kR, dP[c], fma(kP, r[c], tl[3 + c]));
+                        }
+                        psi = P * R0;
+                        q = -fma(Pg, R0, xg * PR1) - half * fma(lapP, R0, fma(al.h46, PR1, rho * PR2));
+                    } else {
+                        T d[14];
+                        ao_lane_components<T, NPR>(al, x, y, z, rho, R0, u1, u2, u3, d);
+                        const T hgx = gx * d[5] + gy * d[6] + gz * d[7];
+                        const T hgy = gx * d[6] + gy * d[8] + gz * d[9];
+                        const T hgz = gx * d[7] + gy * d[9] + gz * d[10];
+                        const T t6[6] = {av * d[1] - kv * (hgx + half * d[11]), av * d[2] - kv * (hgy + half * d[12]),
+                                         av * d[3] - kv * (hgz + half * d[13]), kv * d[1], kv * d[2], kv * d[3]};
+                        psi = d[0];
+                        q = -(gx * d[1] + gy * d[2] + gz * d[3]) - half * d[4];
+#pragma unroll
+                        for (int c = 0; c < 6; ++c) tl[c] += t6[c];
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) t[3 * v + c] = t6[c];
+                    }
+                    const T *kb = Ks + e * ldk + ml;
+                    const T *ab = As + e * ldk + ml;
+#pragma unroll
+                    for (int it = 0; it < NT; ++it) {
+                        const T bk = kb[16 * it], ba = ab[16 * it];
+                        accO[it] = MF::fma(psi, bk, accO[it]);
+                        accG[it] = MF::fma(psi, ba, accG[it]);
+                        accG[it] = MF::fma(q, bk, accG[it]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
                 }
+                // AO sums of t_k over the 16 lanes of a row group (a DPP row),
+                // added to the electron's by one lane each
+                const double dd = (double)row16_sums<T>(t, ml);
+                const int e = 16 * rt + MF::row(0, h) + de;
+                if (dmine && e < N) dw[3 * e + dc] += dd;
+#pragma unroll
+                for (int v = 0; v + VU < 4; ++v) kap[v] = kap[v + VU], aa[v] = aa[v + VU];
             }
         }
         // outer products of the walker for this sub-tile
@@ -180,7 +392,7 @@ __global__ __launch_bounds__(512) void k_adjoint_mfma(SysDev S, const T *__restr
     double *dpart = mb.dedr_part + (size_t)w * N * 3;
     for (int k = tid; k < 3 * N; k += blockDim.x) {
         double acc = 0.0;
-        for (int q = 0; q < nw; ++q) acc += dpw[(size_t)q * 3 * N + k];
+        for (int q = 0; q < nw; ++q) acc += dpw[q * dst + k];
         dpart[k] = acc;
     }
 }
@@ -189,19 +401,29 @@ template <typename T>
 hipError_t launch_adjoint(const SysDev &S, const T *C, const double *R, const MeasBufs<T> &mb,
                           const WalkerOut &out, const AdjLayout &L, int W, hipStream_t st) {
     const dim3 g((unsigned)W), b((unsigned)(64 * L.waves));
+    constexpr bool SH = sizeof(T) == 8;
+#define ADJ(NT, SHARED) hipLaunchKernelGGL((k_adjoint_mfma<T, NT, SHARED>), g, b, L.bytes, st, S, C, R, mb, out, L)
     switch ((S.n_occ + 15) / 16) {
-        case 1: hipLaunchKernelGGL((k_adjoint_mfma<T, 1>), g, b, L.bytes, st, S, C, R, mb, out, L); break;
-        case 2: hipLaunchKernelGGL((k_adjoint_mfma<T, 2>), g, b, L.bytes, st, S, C, R, mb, out, L); break;
-        case 3: hipLaunchKernelGGL((k_adjoint_mfma<T, 3>), g, b, L.bytes, st, S, C, R, mb, out, L); break;
-        default: hipLaunchKernelGGL((k_adjoint_mfma<T, 4>), g, b, L.bytes, st, S, C, R, mb, out, L); break;
+        case 1: ADJ(1, SH); break;
+        case 2: ADJ(2, SH); break;
+        case 3: ADJ(3, SH); break;
+        default:
+            if (SH && L.shared)
+                ADJ(4, SH);
+            else
+                ADJ(4, false);
+            break;
     }
+#undef ADJ
     return hipGetLastError();
 }
 
 template <typename T>
 hipError_t configure_adjoint(size_t lds) {
-    const void *f[4] = {(const void *)k_adjoint_mfma<T, 1>, (const void *)k_adjoint_mfma<T, 2>,
-                        (const void *)k_adjoint_mfma<T, 3>, (const void *)k_adjoint_mfma<T, 4>};
+    constexpr bool SH = sizeof(T) == 8;
+    const void *f[5] = {(const void *)k_adjoint_mfma<T, 1, SH>, (const void *)k_adjoint_mfma<T, 2, SH>,
+                        (const void *)k_adjoint_mfma<T, 3, SH>, (const void *)k_adjoint_mfma<T, 4, SH>,
+                        (const void *)k_adjoint_mfma<T, 4, false>};
     for (const void *g : f) {
         const hipError_t e = hipFuncSetAttribute(g, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;

@@ -33,12 +33,19 @@ struct DenseLayout {
     size_t bytes;
 };
 
+// Shells of k_adjoint_mfma's shared radial sums at a time (odd: no bank
+// conflicts; a sub-tile of 16 AOs mostly holds parts of 7 shells)
+constexpr int ADJ_XS = 7;
+
 // LDS layout of k_adjoint_mfma (bytes).
 struct AdjLayout {
     int ldk;                         // row stride (elements, odd) of K~ and Abar
     int rt;                          // 16-electron row tiles
     int off_k, off_a, off_p, off_g, off_d;
-    int waves;                       // wavefronts per block
+    bool shared;                     // room for the radial sums that a sub-tile's AOs share
+    // wavefronts per block (the same for every launch: a walker's dE_L/dr adds
+    // their partials in order, and its bits do not depend on the launch)
+    int waves;
     size_t bytes;
 };
 
