@@ -299,12 +299,14 @@ static void layouts(vmc_ctx *c) {
     d.ldk = kn + 1;
     d.off_p = 0;
     d.off_g = d.off_p + al((size_t)3 * N * 8);
-    d.off_k = d.off_g + al((size_t)3 * N * 8);
-    d.off_x = d.off_k + al((size_t)2 * kn * d.ldk * 8);
-    d.off_perm = d.off_x + al((size_t)kn * d.ldk * 8);
+    d.off_x = d.off_g + al((size_t)3 * N * 8);
+    // (X's place first holds the pair tables)
+    const int nw = vmcx::dense_waves(kn), ng = 64 * nw / vmcx::dense_pair_lanes(kn);
+    d.off_perm = d.off_x + al((size_t)std::max(kn * d.ldk, (ng + std::max(ng, nw)) * 3 * N) * 8);
     d.off_red = d.off_perm + al(128 * 4);
-    d.off_jas = d.off_red + al(16 * 8);
-    d.bytes = (size_t)d.off_jas + (size_t)(2 + 4) * N * 3 * 8;
+    d.off_k = d.off_red + al(24 * 8);
+    d.bytes_one = (size_t)d.off_k + al((size_t)kn * d.ldk * 8);
+    d.bytes = (size_t)d.off_k + 2 * al((size_t)kn * d.ldk * 8);
 }
 
 // Walkers per measurement launch: W split into the fewest chunks that fit

@@ -110,27 +110,6 @@ __device__ inline void ao_lane_monomial(const AoLane<T, NPR> &L, T x, T y, T z, 
     HPg[2] = fma(Pxz, gx, fma(Pyz, gy, Pzz * gz));
 }
 
-// keep + the partner's send, the partner being lane ^ K of the DPP row
-template <int K>
-__device__ inline int row_xor(int v) {
-    if (K == 1) return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);   // quad_perm [1, 0, 3, 2]
-    if (K == 2) return __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);   // quad_perm [2, 3, 0, 1]
-    if (K == 8) return __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true);  // row_ror 8
-    // lanes 0-3 and 8-11 of the row from 4 above, the others from 4 below
-    const int up = __builtin_amdgcn_update_dpp(0, v, 0x104, 0xF, 0x5, true);
-    return __builtin_amdgcn_update_dpp(up, v, 0x114, 0xF, 0xA, true);
-}
-template <int K>
-__device__ inline float add_xor(float keep, float send) {
-    return keep + __int_as_float(row_xor<K>(__float_as_int(send)));
-}
-template <int K>
-__device__ inline double add_xor(double keep, double send) {
-    const long long b = __double_as_longlong(send);
-    const int lo = row_xor<K>((int)b), hi = row_xor<K>((int)(b >> 32));
-    return keep + __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-
 // Sums of 3 or 6 values over the 16 lanes of a DPP row, one value a lane, by
 // halving what a lane holds at each step: lane m (of the row) returns the value
 // row16_which<NV>(m).  The pairs added are those of row16_sum_last (neighbours,

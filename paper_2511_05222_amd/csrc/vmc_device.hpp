@@ -402,6 +402,55 @@ __device__ inline double wave_sum_dpp(double v) {
     return (r[0] + r[1]) + (r[2] + r[3]);
 }
 
+// keep + the partner's send, the partner being lane ^ K of the DPP row
+template <int K>
+__device__ inline int row_xor(int v) {
+    if (K == 1) return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);   // quad_perm [1, 0, 3, 2]
+    if (K == 2) return __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);   // quad_perm [2, 3, 0, 1]
+    if (K == 8) return __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true);  // row_ror 8
+    // lanes 0-3 and 8-11 of the row from 4 above, the others from 4 below
+    const int up = __builtin_amdgcn_update_dpp(0, v, 0x104, 0xF, 0x5, true);
+    return __builtin_amdgcn_update_dpp(up, v, 0x114, 0xF, 0xA, true);
+}
+template <int K>
+__device__ inline float add_xor(float keep, float send) {
+    return keep + __int_as_float(row_xor<K>(__float_as_int(send)));
+}
+template <int K>
+__device__ inline double add_xor(double keep, double send) {
+    const long long b = __double_as_longlong(send);
+    const int lo = row_xor<K>((int)b), hi = row_xor<K>((int)(b >> 32));
+    return keep + __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
+// v plus that of the lane 16 (32) away, in every lane: the swap leaves the two
+// rows (halves) of each pair in both of its results.
+__device__ inline double add_rows16(double v) {
+    const long long b = __double_as_longlong(v);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+    return __longlong_as_double(((long long)hi[0] << 32) | lo[0]) +
+           __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+__device__ inline double add_rows32(double v) {
+    const long long b = __double_as_longlong(v);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+    return __longlong_as_double(((long long)hi[0] << 32) | lo[0]) +
+           __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+
+// Sums of four values over the wavefront, halving what a lane holds at each of
+// the first two steps: lane m returns the sum of t[m & 3].
+__device__ inline double wave_sum4(const double *t, int m) {
+    const double q0 = add_xor<1>((m & 1) ? t[1] : t[0], (m & 1) ? t[0] : t[1]);
+    const double q1 = add_xor<1>((m & 1) ? t[3] : t[2], (m & 1) ? t[2] : t[3]);
+    double u = add_xor<2>((m & 2) ? q1 : q0, (m & 2) ? q0 : q1);
+    u = add_xor<4>(u, u);
+    u = add_xor<8>(u, u);
+    return add_rows32(add_rows16(u));
+}
+
 // All cartesian components of a shell at an electron, with the angular
 // momentum fixed at compile time so that every component index (and the
 // component factor: 1/sqrt(3) for xx, yy, zz, else 1) is a constant and nothing

@@ -27,10 +27,15 @@ struct SweepLayout {
 };
 
 // LDS layout of k_dense (bytes).
+// k_dense's blocks for spin blocks of up to kn orbitals: wavefronts, and lanes
+// of a group that takes a round of electron pairs (at least 2 kn electrons)
+constexpr int dense_waves(int kn) { return kn == 64 ? 8 : 4; }
+constexpr int dense_pair_lanes(int kn) { return kn == 16 ? 32 : (kn == 32 ? 64 : 128); }
+
 struct DenseLayout {
     int ldk;                 // row stride (doubles, odd) of K, X and T
-    int off_p, off_g, off_k, off_x, off_perm, off_red, off_jas;
-    size_t bytes;
+    int off_p, off_g, off_x, off_perm, off_red, off_k;
+    size_t bytes, bytes_one;   // both spin blocks' inverses, one of them
 };
 
 // Shells of k_adjoint_mfma's shared radial sums at a time (odd: no bank
