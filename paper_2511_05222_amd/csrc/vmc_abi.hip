@@ -415,7 +415,7 @@ static int measure_core(vmc_ctx *c, const double *pos, const double *pos0, int64
         const int pg = prof_begin(c, VMC_K_JAS_GEMM, prof, cw, st);
         HIP_OK(c, vmcx::launch_jas_hxi<T>(c->MJ, c->nq, jrows, jD, c->mb_gb, xi_blocks<T>(c), jQ, st));
         prof_end(c, VMC_K_JAS_GEMM, pg, st);
-        HIP_OK(c, vmcx::launch_jas_adjoint<T>(c->jdev, R, c->N, jrows, 0, (int)cw, pos, jV, jQ, c->mb_gb, c->d_xi1,
+        HIP_OK(c, vmcx::launch_jas_adjoint<T>(c->jdev, R, c->A, c->N, jrows, 0, (int)cw, pos, jV, jQ, c->mb_gb, c->d_xi1,
                                               c->mb_dpart, c->jm_tao, st));
         md.jtao = c->jm_tao;
         md.jb = c->jdev;

@@ -38,6 +38,7 @@ namespace vmcx {
 
 constexpr int JAS_MAX = 256;   // Jastrow basis functions
 constexpr int JAS_ELEC = 128;  // electrons
+constexpr int JAS_ATOMS = 64;  // nuclei
 
 // out[row][mu] = chi_mu(pos[row]) for the rows' positions and, with NC = 5,
 // der[row][c][mu] = (d/dx, d/dy, d/dz, Laplacian)_c chi_mu(pos[row]); one
@@ -183,9 +184,12 @@ __global__ __launch_bounds__(256) void k_jas_assemble(int N, int MJ, int64_t row
 // The LDS chunk is laid out [k][m][tile] (rows of NTL + 16 bytes), so that a
 // lane reads its NTL B entries of a step as 16-byte vectors without bank
 // conflicts.  The xi1 column (AM 0, 1) is a dot product per row: lane
-// partial sums over its k, added over the four lanes of the row.
+// partial sums over its k, added over the four lanes of the row.  Bound: the
+// matrix cores and, AM 2, HBM (0.66 and 0.93 ms at their rates for 770000 rows
+// of 256); FP32 at three wavefronts a SIMD, a few registers spilled, 1.29, 1.11
+// and 1.25 ms for AM 1, 0, 2, at two 1.32, 1.23 and 1.33.
 template <typename T, int NTL, int AM, bool VA>
-__global__ __launch_bounds__(256) void k_jas_gemm(int MJ, int64_t rows, const T *__restrict__ A0,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 1))) void k_jas_gemm(int MJ, int64_t rows, const T *__restrict__ A0,
                                                   const T *__restrict__ A1, const double *__restrict__ gb,
                                                   const T *__restrict__ xiblk, T *__restrict__ out) {
     typedef Mfma<T> MF;
@@ -340,19 +344,62 @@ __global__ __launch_bounds__(256) void k_jas_gemm(int MJ, int64_t rows, const T 
     }
 }
 
-// The 14 derivative components (value, gradient, Laplacian, Hessian,
-// gradient of the Laplacian) of Jastrow function mu at (x, y, z): the lane's
-// function data as in the adjoint's AO lanes (monomial as branch-free
-// per-axis quadratics; the first primitive in registers in FP32, the
-// Jastrow basis being uncontracted).
+// What a lane keeps of a Jastrow function across electrons: monomial powers and
+// angular momentum packed, and (FP32) the first primitive, the Jastrow basis
+// being uncontracted.
 template <typename T>
-__device__ inline void jas_function14(const BasisDev &JB, const double *R, int mu, double x, double y, double z,
-                                      T *c) {
+struct JasFn {
+    int pk, np, p0, atom;   // pk: powers (12 bits) | l << 12
+    T eta, al, cp;
+};
+
+template <typename T>
+__device__ inline JasFn<T> jas_fn(const BasisDev &JB, int mu) {
+    const int s = JB.ao_shell[mu];
+    JasFn<T> f;
+    f.pk = JB.ao_pow[mu] | (JB.shell_l[s] << 12);
+    f.np = JB.shell_np[s];
+    f.p0 = JB.shell_p0[s];
+    f.atom = JB.shell_atom[s];
+    f.eta = (T)JB.ao_eta[mu];
+    f.al = (T)JB.prim_exp[f.p0];
+    f.cp = (T)JB.prim_cp[f.p0];
+    return f;
+}
+
+// The 14 derivative components (value, gradient, Laplacian, Hessian,
+// gradient of the Laplacian) of a Jastrow function at displacement d from its
+// nucleus, as in the adjoint's AO lanes (monomial as branch-free per-axis
+// quadratics; the first primitive from registers in FP32).
+template <typename T>
+__device__ inline void jas_function14(const BasisDev &JB, const JasFn<T> &f, double dx, double dy, double dz, T *c) {
     constexpr int NPR = sizeof(T) == 4 ? 1 : 0;
     AoLane<T, NPR> al;
-    ao_lane_load<T, NPR>(JB, mu, al);
-    const int atom = JB.shell_atom[JB.ao_shell[mu]];
-    const double dx = x - R[3 * atom], dy = y - R[3 * atom + 1], dz = z - R[3 * atom + 2];
+    // (unpacked each time: kept, the coefficients of four functions would be
+    // live)
+    int pk = f.pk;
+    asm volatile("" : "+v"(pk));
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const int p = (pk >> (4 * q)) & 15;
+        const T sc = q == 0 ? f.eta : T(1);
+        al.c0[q] = p == 0 ? sc : T(0);
+        al.c1[q] = p == 1 ? sc : T(0);
+        al.c2[q] = p == 2 ? sc : T(0);
+        al.c22[q] = al.c2[q] + al.c2[q];
+    }
+    const int l = pk >> 12;
+    al.h46 = T(2 * l + 3);
+    al.h820 = T(2 * l + 5);
+    al.np = f.np;
+    al.p0 = f.p0;
+    if constexpr (NPR == 1) {
+        al.al[0] = f.al;
+        al.al2[0] = f.al * f.al;
+        al.al3[0] = al.al2[0] * f.al;
+        al.cp[0] = f.cp;
+        al.alt[0] = (double)f.al * 1.4426950408889634;
+    }
     const double rho_d = dx * dx + dy * dy + dz * dz;
     T R0, u1, u2, u3;
     ao_lane_radial<T, NPR>(al, JB, rho_d, R0, u1, u2, u3);
@@ -367,10 +414,10 @@ struct JasTerm {
 };
 
 template <typename T>
-__device__ inline JasTerm<T> jas_term(const BasisDev &JB, const double *R, int mu, const double *pe, const T *ab, T g,
-                                      T q) {
+__device__ inline JasTerm<T> jas_term(const BasisDev &JB, const JasFn<T> &fn, const double *Ra, const double *pe,
+                                      const T *ab, T g, T q) {
     T c[14];
-    jas_function14<T>(JB, R, mu, pe[0], pe[1], pe[2], c);
+    jas_function14<T>(JB, fn, pe[0] - Ra[0], pe[1] - Ra[1], pe[2] - Ra[2], c);
     JasTerm<T> o;
     const T hs[3][3] = {{c[5], c[6], c[7]}, {c[6], c[8], c[9]}, {c[7], c[9], c[10]}};
 #pragma unroll
@@ -390,9 +437,12 @@ __device__ inline JasTerm<T> jas_term(const BasisDev &JB, const double *R, int m
 // mu = lane + 64 k; per electron the sum over functions by a wavefront sum,
 // per function the wavefronts' partial sums added in wavefront order.  The
 // terms and the sums inside a wavefront are in the arithmetic type, FP64 from
-// the wavefront sums on.
+// the wavefront sums on.  Bound: latency of loads, where the vector units are
+// busy two fifths of the time; a lane's functions and the next electron's values
+// are held ahead of their use, at three wavefronts a SIMD (256 functions, 94
+// electrons, 8192 walkers FP32: 1.87 -> 1.11 ms).
 template <typename T>
-__global__ __launch_bounds__(256) void k_jas_adjoint(BasisDev JB, const double *__restrict__ R, int N, int MJ,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 1))) void k_jas_adjoint(BasisDev JB, const double *__restrict__ R, int A, int N, int MJ,
                                                      int64_t rows, int64_t row0, const double *__restrict__ pos,
                                                      const T *__restrict__ V, const T *__restrict__ Q,
                                                      const double *__restrict__ gb, const double *__restrict__ xi1,
@@ -400,6 +450,7 @@ __global__ __launch_bounds__(256) void k_jas_adjoint(BasisDev JB, const double *
     __shared__ double tv[JAS_MAX], xh[JAS_MAX];
     __shared__ double ab[JAS_ELEC * 3], pe[JAS_ELEC * 3], fe[JAS_ELEC * 3];
     __shared__ double fp[JAS_MAX * 6];
+    __shared__ double Rs[JAS_ATOMS * 3];
     const int w = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // the value products and Q = xi3 h of electron e
     auto Vat = [&](int e, int mu) -> double {
@@ -411,13 +462,25 @@ __global__ __launch_bounds__(256) void k_jas_adjoint(BasisDev JB, const double *
         ab[i] = -(gb[((size_t)w * N + e) * 6 + d] + gb[((size_t)w * N + e) * 6 + 3 + d]);
         pe[i] = pos[(size_t)w * N * 3 + i];
     }
+    for (int i = tid; i < 3 * A; i += 256) Rs[i] = R[i];
     __syncthreads();
     // t = xi3 s (the value products summed over electrons) and xi3 H
+    // (eight electrons' values in flight: one latency for each, not for all)
     for (int mu = tid; mu < MJ; mu += 256) {
         double t = 0.0, h = 0.0;
-        for (int e = 0; e < N; ++e) {
-            t += Vat(e, mu);
-            h += Qat(e, mu);
+        for (int e0 = 0; e0 < N; e0 += 8) {
+            double v[8], q[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                v[u] = Vat(min(e0 + u, N - 1), mu);
+                q[u] = Qat(min(e0 + u, N - 1), mu);
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (e0 + u < N) {
+                    t += v[u];
+                    h += q[u];
+                }
         }
         tv[mu] = t;
         xh[mu] = h;
@@ -428,21 +491,45 @@ __global__ __launch_bounds__(256) void k_jas_adjoint(BasisDev JB, const double *
     for (int k = 0; k < 4; ++k)
 #pragma unroll
         for (int d = 0; d < 3; ++d) F[k][d] = P[k][d] = T(0);
+    // (the functions' tables are read once: looked up for each electron, four
+    // dependent loads an evaluation took most of the time)
+    JasFn<T> fn[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) fn[k] = jas_fn<T>(JB, min(lane + 64 * k, MJ - 1));
+    // (the next electron's values are loaded while one is evaluated)
+    T vn[4], qn[4];
+    auto fetch = [&](int e) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int mu = min(lane + 64 * k, MJ - 1);
+            vn[k] = (T)Vat(min(e, N - 1), mu);
+            qn[k] = (T)Qat(min(e, N - 1), mu);
+        }
+    };
+    fetch(wave);
     for (int e = wave; e < N; e += 4) {
         const T a[3] = {(T)ab[3 * e], (T)ab[3 * e + 1], (T)ab[3 * e + 2]};
         T f3[3] = {T(0), T(0), T(0)};
+        double vc[4], qc[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            vc[k] = (double)vn[k];
+            qc[k] = (double)qn[k];
+        }
+        fetch(e + 4);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int mu = lane + 64 * k;
             if (mu >= MJ) continue;
-            const T g = (T)(xi1[mu] + tv[mu] - Vat(e, mu)), q = (T)(xh[mu] - Qat(e, mu));
-            const JasTerm<T> o = jas_term<T>(JB, R, mu, pe + 3 * e, a, g, q);
+            const T g = (T)(xi1[mu] + tv[mu] - vc[k]), q = (T)(xh[mu] - qc[k]);
+            const JasTerm<T> o = jas_term<T>(JB, fn[k], Rs + 3 * fn[k].atom, pe + 3 * e, a, g, q);
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
                 F[k][d] += o.f[d];
                 P[k][d] += o.p[d];
                 f3[d] += o.f[d];
             }
+            __builtin_amdgcn_sched_barrier(0);   // one function's evaluation at a time: registers
         }
         double f3d[3];
 #pragma unroll
@@ -536,10 +623,10 @@ hipError_t launch_jas_hxi(int MJ, int /* nq */, int64_t rows, const T *D, const 
 }
 
 template <typename T>
-hipError_t launch_jas_adjoint(const BasisDev &JB, const double *R, int N, int64_t rows, int64_t row0, int W,
+hipError_t launch_jas_adjoint(const BasisDev &JB, const double *R, int A, int N, int64_t rows, int64_t row0, int W,
                               const double *pos, const T *V, const T *Q, const double *gb, const double *xi1,
                               double *dedr, double *jtao, hipStream_t st) {
-    hipLaunchKernelGGL(k_jas_adjoint<T>, dim3((unsigned)W), dim3(256), 0, st, JB, R, N, JB.n_ao, rows, row0, pos, V,
+    hipLaunchKernelGGL(k_jas_adjoint<T>, dim3((unsigned)W), dim3(256), 0, st, JB, R, A, N, JB.n_ao, rows, row0, pos, V,
                        Q, gb, xi1, dedr, jtao);
     return hipGetLastError();
 }
@@ -553,7 +640,7 @@ hipError_t launch_jas_adjoint(const BasisDev &JB, const double *R, int N, int64_
                                                const T *, const double *, double *, double *, hipStream_t);        \
     template hipError_t launch_jas_hxi<T>(int, int, int64_t, const T *, const double *, const T *, T *,           \
                                           hipStream_t);                                                            \
-    template hipError_t launch_jas_adjoint<T>(const BasisDev &, const double *, int, int64_t, int64_t, int,       \
+    template hipError_t launch_jas_adjoint<T>(const BasisDev &, const double *, int, int, int64_t, int64_t, int,       \
                                               const double *, const T *, const T *, const double *,               \
                                               const double *, double *, double *, hipStream_t);
 JAS_INST(float)

@@ -186,7 +186,7 @@ template <typename T>
 hipError_t launch_jas_hxi(int MJ, int nq, int64_t rows, const T *D, const double *gb, const T *xiblk, T *Q,
                           hipStream_t st);
 template <typename T>
-hipError_t launch_jas_adjoint(const BasisDev &JB, const double *R, int N, int64_t rows, int64_t row0, int W,
+hipError_t launch_jas_adjoint(const BasisDev &JB, const double *R, int A, int N, int64_t rows, int64_t row0, int W,
                               const double *pos, const T *V, const T *Q, const double *gb, const double *xi1,
                               double *dedr, double *jtao, hipStream_t st);
 // The launch's sums of the Jastrow-parameter log-derivatives (weights wt,
