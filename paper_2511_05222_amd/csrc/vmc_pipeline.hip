@@ -29,7 +29,8 @@ struct WarpE {
 __device__ inline WarpE warp_electron(const double *R0, int A, double x, double y, double z) {
     WarpE o;
     o.near = -1;
-    double S = 0.0;
+    // (one pass: S = sum kappa and the sum of kappa d^-2 (r - R_b))
+    double S = 0.0, gx = 0.0, gy = 0.0, gz = 0.0;
     for (int b = 0; b < A; ++b) {
         const double dx = x - R0[3 * b], dy = y - R0[3 * b + 1], dz = z - R0[3 * b + 2];
         const double d2 = dx * dx + dy * dy + dz * dz;
@@ -38,20 +39,17 @@ __device__ inline WarpE warp_electron(const double *R0, int A, double x, double 
             o.near = b;
         else
             id2 = rcp_nr(d2);
-        S += id2 * id2;
+        const double k = id2 * id2, f = k * id2;
+        S += k;
+        gx = fma(f, dx, gx);
+        gy = fma(f, dy, gy);
+        gz = fma(f, dz, gz);
     }
     o.invS = 1.0 / S;
-    o.sg[0] = o.sg[1] = o.sg[2] = 0.0;
-    if (o.near < 0)
-        for (int b = 0; b < A; ++b) {
-            const double dx = x - R0[3 * b], dy = y - R0[3 * b + 1], dz = z - R0[3 * b + 2];
-            const double id2 = rcp_nr(dx * dx + dy * dy + dz * dz);
-            const double om = o.invS * id2 * id2;
-            const double f = -4.0 * id2;
-            o.sg[0] += om * f * dx;
-            o.sg[1] += om * f * dy;
-            o.sg[2] += om * f * dz;
-        }
+    const double f = o.near < 0 ? -4.0 * o.invS : 0.0;
+    o.sg[0] = o.near < 0 ? f * gx : 0.0;
+    o.sg[1] = o.near < 0 ? f * gy : 0.0;
+    o.sg[2] = o.near < 0 ? f * gz : 0.0;
     return o;
 }
 
@@ -115,8 +113,12 @@ __global__ __launch_bounds__(128) void k_warp(SysDev S, const double *__restrict
 // k_finalize: one block per walker.
 // ---------------------------------------------------------------------------
 // doubles of the region that holds Minv [N][9] and wS [N][4], then the
-// [128][9] partial sums of the per-nucleus phase
+// [128][9] partial sums of the per-nucleus phase; before them the pairs' tables
+// (at most 8 x 3 N of 32 electrons, 4 of 64, 3 of more)
 __host__ __device__ inline int finalize_region(int N) { return 13 * N > 128 * 9 ? 13 * N : 128 * 9; }
+// lanes of a group over electron pairs, and the tables of their sums
+__host__ __device__ inline int finalize_lanes(int N) { return N <= 32 ? 32 : (N <= 64 ? 64 : 128); }
+__host__ __device__ inline int finalize_tables(int N) { return N <= 32 ? 4 : 2; }
 
 __global__ __launch_bounds__(128) void k_finalize(SysDev S, const double *__restrict__ R,
                                                   const double *__restrict__ R0, MeasBufsD mb,
@@ -127,79 +129,89 @@ __global__ __launch_bounds__(128) void k_finalize(SysDev S, const double *__rest
     const int N = S.N, A = S.A, M = S.M;
     double *p = smem;              // [N][3] evaluation positions
     double *p0 = p + 3 * N;        // [N][3] sampling positions
-    double *gb = p0 + 3 * N;       // [N][6]
-    double *dEdr = gb + 6 * N;     // [N][3]
+    double *gt = p0 + 3 * N;       // [N][3] total gradient (Jastrow + determinant)
+    double *dEdr = gt + 3 * N;     // [N][3]
     double *Minv = dEdr + 3 * N;   // [N][9]
     double *wS = Minv + 9 * N;     // [N][4]: invS, sg
     // (Minv and wS, at least 128 x 9 doubles, later hold the partial sums)
-    double *bw = Minv + finalize_region(N);   // [2][N][3] pair terms gathered by each wavefront
-    int *wnear = (int *)(bw + 6 * N);
-    const int wave = tid >> 6;
+    // pairs: groups of gl threads, a table per group (per wavefront of one group)
+    const int gl = finalize_lanes(N), ntab = finalize_tables(N), ng = 128 / gl;
+    // (their place is Minv's before that is known)
+    double *jp = Minv;              // [ng][N][3] pair terms kept
+    double *bw = jp + ng * 3 * N;   // [ntab][N][3] pair terms gathered
+    int *wnear = (int *)(Minv + finalize_region(N));
     for (int i = tid; i < 3 * N; i += 128) {
         p[i] = mb.pos[(size_t)w * N * 3 + i];
         p0[i] = mb.pos0[(size_t)w * N * 3 + i];
     }
-    for (int i = tid; i < 6 * N; i += 128) gb[i] = mb.gb[(size_t)w * N * 6 + i];
-    for (int i = tid; i < 6 * N; i += 128) bw[i] = 0.0;
+    for (int i = tid; i < 3 * N; i += 128) {
+        const double *gb = mb.gb + (size_t)w * N * 6 + 6 * (i / 3) + i % 3;
+        gt[i] = gb[3] + gb[0];
+    }
+    for (int i = tid; i < ntab * 3 * N; i += 128) bw[i] = 0.0;
     __syncthreads();
     // Electron-electron terms of dE_L/dr, each pair once: the term of pair
-    // (e, k) is odd under the exchange of e and k (bit for bit: every
-    // difference and product in it changes sign exactly), so round s pairs
-    // thread e with k = (e + s) mod N, adds the term to e and subtracts it
-    // from k's slot in its wavefront's table (a permutation of the slots in
-    // every round, read and written in program order).  Rounds s = 1 .. N/2
-    // cover every pair once; in round N/2 of an even N only e < N/2 takes part.
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-    if (tid < N) {
-        const int e = tid;
-        const double x = p[3 * e], y = p[3 * e + 1], z = p[3 * e + 2];
-        const double ge[3] = {-(gb[6 * e + 3] + gb[6 * e]), -(gb[6 * e + 4] + gb[6 * e + 1]),
-                              -(gb[6 * e + 5] + gb[6 * e + 2])};
-        double *bme = bw + (size_t)wave * 3 * N;
-        for (int s = 1; 2 * s <= N; ++s) {
-            if (2 * s == N && e >= s) break;
-            int k = e + s;
-            if (k >= N) k -= N;
-            double d0 = 0.0, d1 = 0.0, d2 = 0.0;
-            const double dx = x - p[3 * k], dy = y - p[3 * k + 1], dz = z - p[3 * k + 2];
-            const double ir = rsqrt_nr(dx * dx + dy * dy + dz * dz);
-            const double r = (dx * dx + dy * dy + dz * dz) * ir;
-            const double ux = dx * ir, uy = dy * ir, uz = dz * ir;
-            const JasD pd = jas_all(r, S.ee_a, S.ee_F, S.ee_form);
-            const double vx = ge[0] + (gb[6 * k + 3] + gb[6 * k]);
-            const double vy = ge[1] + (gb[6 * k + 4] + gb[6 * k + 1]);
-            const double vz = ge[2] + (gb[6 * k + 5] + gb[6 * k + 2]);
-            const double dv = ux * vx + uy * vy + uz * vz;
-            const double f1 = pd.u1 * ir;
-            d0 += pd.u2 * ux * dv + f1 * (vx - ux * dv);
-            d1 += pd.u2 * uy * dv + f1 * (vy - uy * dv);
-            d2 += pd.u2 * uz * dv + f1 * (vz - uz * dv);
-            const double wp1 = pd.u3 + 2.0 * pd.u2 * ir - 2.0 * pd.u1 * ir * ir;
-            d0 -= wp1 * ux;
-            d1 -= wp1 * uy;
-            d2 -= wp1 * uz;
-            const double ir3 = ir * ir * ir;
-            d0 -= dx * ir3;
-            d1 -= dy * ir3;
-            d2 -= dz * ir3;
-            a0 += d0;
-            a1 += d1;
-            a2 += d2;
-            bme[3 * k] -= d0;
-            bme[3 * k + 1] -= d1;
-            bme[3 * k + 2] -= d2;
-            // the next round's partner slot of lane e - 1 is this round's of
-            // lane e: keep the rounds' LDS accesses in order
-            wave_sync_s();
+    // (e, k) is odd under the exchange of e and k, so round s pairs electron e
+    // with k = (e + s) mod N, adds the term to e and subtracts it from k's slot
+    // in a table (a permutation of the slots in every round, read and written
+    // in program order).  Rounds s = 1 .. N/2 cover every pair once; in round
+    // N/2 of an even N only e < N/2 takes part.  The groups share the rounds.
+    // With r = |r_e - r_k|, n = (r_e - r_k) / r, v the difference of the total
+    // gradients and f = u' / r the term is
+    //   n ((u'' - f) (n.v - 2 / r) - u''' - 1 / r^2) + f v,
+    // half of the operations of its parts one by one.  Bound: FP64 issue (94
+    // electrons, 32768 walkers: 1.03 ms at four wavefronts a SIMD, which the small
+    // LDS allows; part by part at three 1.32).
+    {
+        const int h = tid / gl, e = tid - h * gl;
+        double *bme = bw + (gl == 32 ? h : tid >> 6) * 3 * N;
+        const int per = (N / 2 + ng - 1) / ng, s0 = 1 + h * per, s1 = min(N / 2, s0 + per - 1);
+        if (e < N) {
+            double a0 = 0.0, a1 = 0.0, a2 = 0.0;
+            const double x = p[3 * e], y = p[3 * e + 1], z = p[3 * e + 2];
+            const double gx = gt[3 * e], gy = gt[3 * e + 1], gz = gt[3 * e + 2];
+            for (int s = s0; s <= s1; ++s) {
+                if (2 * s == N && e >= s) break;
+                int k = e + s;
+                if (k >= N) k -= N;
+                const double dx = x - p[3 * k], dy = y - p[3 * k + 1], dz = z - p[3 * k + 2];
+                const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
+                const double ir = rsqrt_nr(r2);
+                const double ux = dx * ir, uy = dy * ir, uz = dz * ir;
+                const JasD pd = jas_all(r2 * ir, S.ee_a, S.ee_F, S.ee_form);
+                const double vx = gt[3 * k] - gx, vy = gt[3 * k + 1] - gy, vz = gt[3 * k + 2] - gz;
+                const double f = pd.u1 * ir, t = fma(-2.0, ir, fma(ux, vx, fma(uy, vy, uz * vz)));
+                const double c = fma(pd.u2 - f, t, -fma(ir, ir, pd.u3));
+                const double d0 = fma(ux, c, f * vx), d1 = fma(uy, c, f * vy), d2 = fma(uz, c, f * vz);
+                a0 += d0;
+                a1 += d1;
+                a2 += d2;
+                bme[3 * k] -= d0;
+                bme[3 * k + 1] -= d1;
+                bme[3 * k + 2] -= d2;
+                // the next round's partner slot of lane e - 1 is this round's
+                // of lane e: keep the rounds' LDS accesses in order
+                wave_sync_s();
+            }
+            double *o = jp + 3 * (h * N + e);
+            o[0] = a0;
+            o[1] = a1;
+            o[2] = a2;
         }
     }
     __syncthreads();
+    double pe[3] = {0.0, 0.0, 0.0};
+    if (tid < N)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            for (int q = 0; q < ng; ++q) pe[c] += jp[3 * (q * N + tid) + c];
+            for (int q = 0; q < ntab; ++q) pe[c] += bw[3 * (q * N + tid) + c];
+        }
+    __syncthreads();   // the tables are read: Minv replaces them
     if (tid < N) {
         const int e = tid;
         const double *dp = mb.dedr_part + ((size_t)w * N + e) * 3;
-        double d0 = dp[0] + (a0 + (bw[3 * e] + bw[3 * N + 3 * e]));
-        double d1 = dp[1] + (a1 + (bw[3 * e + 1] + bw[3 * N + 3 * e + 1]));
-        double d2 = dp[2] + (a2 + (bw[3 * e + 2] + bw[3 * N + 3 * e + 2]));
+        double d0 = dp[0] + pe[0], d1 = dp[1] + pe[1], d2 = dp[2] + pe[2];
         const double x = p[3 * e], y = p[3 * e + 1], z = p[3 * e + 2];
         for (int a = 0; a < A; ++a) {
             const double dx = x - R[3 * a], dy = y - R[3 * a + 1], dz = z - R[3 * a + 2];
@@ -294,7 +306,7 @@ __global__ __launch_bounds__(128) void k_finalize(SysDev S, const double *__rest
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
                 sE[k] += om * dEdr[3 * e + k];
-                sP[k] += om * (gb[6 * e + 3 + k] + gb[6 * e + k]);
+                sP[k] += om * gt[3 * e + k];
                 sJ[k] += Mi[k] * g[0] + Mi[3 + k] * g[1] + Mi[6 + k] * g[2];
             }
         }
@@ -355,8 +367,7 @@ hipError_t launch_finalize(const SysDev &S, const double *R, const double *R0, c
                            const WalkerOut &out, int warp, int W, hipStream_t st) {
     // one electron per thread of the 128 (the spin blocks hold at most 64 each)
     if (S.N > 128) return hipErrorInvalidValue;
-    const size_t lds = sizeof(double) * ((size_t)S.N * (3 + 3 + 6 + 3 + 6) + (size_t)finalize_region(S.N)) +
-                       sizeof(int) * (size_t)S.N;
+    const size_t lds = sizeof(double) * ((size_t)12 * S.N + (size_t)finalize_region(S.N)) + sizeof(int) * (size_t)S.N;
     hipLaunchKernelGGL(k_finalize, dim3(W), dim3(128), lds, st, S, R, R0, mb, out, warp);
     return hipGetLastError();
 }
