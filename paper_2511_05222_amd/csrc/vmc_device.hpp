@@ -451,6 +451,30 @@ __device__ inline double wave_sum4(const double *t, int m) {
     return add_rows32(add_rows16(u));
 }
 
+// Exclusive sum of v over the threads of a block of BS and its total: scans
+// within the wavefronts, then over their totals.
+template <int BS, typename V>
+__device__ inline V block_excl_scan(V v, V *buf, V &total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    V x = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const V y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+    }
+    if (lane == 63) buf[wave] = x;
+    __syncthreads();
+    V before = 0;
+    total = 0;
+#pragma unroll
+    for (int q = 0; q < BS / 64; ++q) {
+        if (q < wave) before += buf[q];
+        total += buf[q];
+    }
+    __syncthreads();
+    return before + x - v;
+}
+
 // All cartesian components of a shell at an electron, with the angular
 // momentum fixed at compile time so that every component index (and the
 // component factor: 1/sqrt(3) for xx, yy, zz, else 1) is a constant and nothing

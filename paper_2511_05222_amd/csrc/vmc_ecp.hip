@@ -146,49 +146,44 @@ __device__ inline int ecp_inside(const EcpDev &E, const double *R, int a, double
 
 __global__ __launch_bounds__(128) void k_ecp_count(SysDev S, EcpDev E, const double *__restrict__ R,
                                                    const double *__restrict__ pos, int *npairs) {
-    __shared__ int cnt[128];
+    __shared__ int cnt[2];
     const int w = blockIdx.x, tid = threadIdx.x, N = S.N;
     const double *p = pos + (size_t)w * N * 3;
     int c = 0;
     if (tid < N)
         for (int k = 0; k < E.n_nl; ++k) c += ecp_inside(E, R, E.nl_atom[k], p[3 * tid], p[3 * tid + 1], p[3 * tid + 2]);
-    cnt[tid] = c;
-    __syncthreads();
-    if (tid == 0) {
-        int s = 0;
-        for (int i = 0; i < N; ++i) s += cnt[i];
-        npairs[w] = s;
-    }
+    int total;
+    block_excl_scan<128>(c, cnt, total);
+    if (tid == 0) npairs[w] = total;
 }
 
 // off[w] = pairs of the walkers before w; a walker's pairs past the
 // launch's capacity are dropped (and flagged); *nrows = 12 * the pairs kept.
 __global__ __launch_bounds__(1024) void k_ecp_scan(int W, int64_t cap, int *npairs, int *off, int *nrows,
                                                    int *status) {
-    __shared__ int64_t part[1024];
+    __shared__ int64_t part[16];
     const int tid = threadIdx.x;
     const int seg = (W + 1023) / 1024, w0 = tid * seg, w1 = min(W, w0 + seg);
     int64_t s = 0;
+#pragma unroll 8
     for (int w = w0; w < w1; ++w) s += npairs[w];
-    part[tid] = s;
-    __syncthreads();
+    int64_t total;
+    int64_t o = block_excl_scan<1024>(s, part, total);
     if (tid == 0) {
-        int64_t t = 0;
-        for (int i = 0; i < 1024; ++i) {
-            const int64_t v = part[i];
-            part[i] = t;
-            t += v;
-        }
-        *nrows = (int)(12 * min(t, cap));
-        if (t > cap) atomicOr(status, STATUS_CAPACITY);
+        *nrows = (int)(12 * min(total, cap));
+        if (total > cap) atomicOr(status, STATUS_CAPACITY);
     }
-    __syncthreads();
-    int64_t o = part[tid];
-    for (int w = w0; w < w1; ++w) {
-        const int c = npairs[w];
-        off[w] = (int)min(o, cap);
-        npairs[w] = (int)max((int64_t)0, min((int64_t)c, cap - o));
-        o += c;
+    for (int wb = w0; wb < w1; wb += 8) {
+        int c[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) c[u] = npairs[min(wb + u, w1 - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (wb + u >= w1) break;
+            off[wb + u] = (int)min(o, cap);
+            npairs[wb + u] = (int)max((int64_t)0, min((int64_t)c[u], cap - o));
+            o += c[u];
+        }
     }
 }
 
@@ -197,27 +192,18 @@ __global__ __launch_bounds__(128) void k_ecp_place(SysDev S, EcpDev E, const dou
                                                    const int *__restrict__ idlist, uint32_t rot,
                                                    const int *__restrict__ npairs, const int *__restrict__ off,
                                                    int *pairs, double *qpos) {
-    __shared__ int cnt[128];
+    __shared__ int cnt[2];
     const int w = blockIdx.x, tid = threadIdx.x, N = S.N;
     const double *p = pos + (size_t)w * N * 3;
     int c = 0;
     if (tid < N)
         for (int k = 0; k < E.n_nl; ++k) c += ecp_inside(E, R, E.nl_atom[k], p[3 * tid], p[3 * tid + 1], p[3 * tid + 2]);
-    cnt[tid] = c;
-    __syncthreads();
-    if (tid == 0) {
-        int s = 0;
-        for (int i = 0; i < 128; ++i) {
-            const int t = cnt[i];
-            cnt[i] = s;
-            s += t;
-        }
-    }
-    __syncthreads();
+    int total;
+    const int first = block_excl_scan<128>(c, cnt, total);
     const int np = npairs[w], o0 = off[w];
     int *pw = pairs + o0;
     if (tid < N) {
-        int o = cnt[tid];
+        int o = first;
         for (int k = 0; k < E.n_nl; ++k) {
             const int a = E.nl_atom[k];
             if (ecp_inside(E, R, a, p[3 * tid], p[3 * tid + 1], p[3 * tid + 2])) {
@@ -584,8 +570,11 @@ __device__ inline void ao_lane_value_grad(const AoLane<T, NPR> &L, T x, T y, T z
 // k_ecp_points_ao (threads over (AO mu, slot), the slots splitting the
 //   points when the AOs are fewer than the threads): G[mu] += sum_q
 //   psi_mu(r_q) y_q and tc[mu] = sum_q kappa_q,mu grad psi_mu(r_q),
-//   kappa_q = C y_q, over batches of 32 points staged in LDS; the slots'
-//   partials added in slot order.
+//   kappa_q = C y_q, over batches of 64 points staged in LDS; the slots'
+//   partials added in slot order.  Bound: issue; the staged y are padded with
+//   zeros to whole 16-byte vectors, so that the sums over orbitals need no
+//   branch and a quarter of the LDS reads, and the partials share their place
+//   (four blocks a CU; 13 orbitals, 16384 walkers FP32: 1.22 -> 1.03 ms).
 // k_ecp_chain:
 //   phase 0 (threads over electrons): jo[e] = sum_{j != e} u'(r_ej) (r_e - r_j)/r_ej;
 //            (threads over pairs) es[e] = the sum of E_q = c'_q t_q over e's
@@ -610,9 +599,11 @@ __global__ __launch_bounds__(256) void k_ecp_points_ao(SysDev S, const T *__rest
     const int w = blockIdx.x, tid = threadIdx.x;
     const int N = S.N, n = S.n_occ, M = S.M;
     const BasisDev &B = S.basis;
+    typedef T V16 __attribute__((ext_vector_type(16 / sizeof(T))));
+    constexpr int VL = 16 / sizeof(T);
     double *sq = sm;               // [RB][3]
-    double *part = sq + 3 * RB;    // [256][16]
-    T *sy = (T *)(part + 256 * 16);   // [RB][n]
+    T *sy = (T *)(sq + 3 * RB);    // [RB][NW], zeros past the orbitals and the points
+    double *part = sm;             // [256][16] once a pass over the points is done
     const int np = eb.npairs[w], nrow = 12 * np;
     const size_t o0 = (size_t)eb.off[w];
     const int *pw = eb.pairs + o0;
@@ -643,14 +634,11 @@ __global__ __launch_bounds__(256) void k_ecp_points_ao(SysDev S, const T *__rest
         T tcx = T(0), tcy = T(0), tcz = T(0);
         for (int r0 = 0; r0 < nrow; r0 += RB) {
             __syncthreads();
-            for (int idx = tid; idx < RB * n; idx += 256) {
-                const int r = idx / n, j = idx - (idx / n) * n, row = r0 + r;
-                double y = 0.0;
-                if (row < nrow) {
-                    const int e = pw[row / 12] & 255;
-                    y = rw[(size_t)row * ECP_ROW] * (double)kt[(size_t)e * n + j];
-                }
-                sy[idx] = (T)y;
+            for (int idx = tid; idx < RB * NW; idx += 256) {
+                const int r = idx / NW, j = idx % NW, row = min(r0 + r, nrow - 1);
+                const int e = pw[row / 12] & 255;
+                const double y = rw[(size_t)row * ECP_ROW] * (double)kt[(size_t)e * n + min(j, n - 1)];
+                sy[idx] = r0 + r < nrow && j < n ? (T)y : T(0);
             }
             for (int idx = tid; idx < 3 * RB; idx += 256) {
                 const int row = r0 + idx / 3;
@@ -668,12 +656,15 @@ __global__ __launch_bounds__(256) void k_ecp_points_ao(SysDev S, const T *__rest
                 ao_lane_radial<T, NPR>(al, B, rho, R0, u1, u2, u3);
                 ao_lane_value_grad<T, NPR>(al, (T)dx, (T)dy, (T)dz, R0, u1, o);
                 T kap = T(0);
-                const T *y = sy + (size_t)r * n;
+                const T *y = sy + r * NW;
 #pragma unroll
-                for (int j = 0; j < NW; ++j) {
-                    const T yj = j < n ? y[j] : T(0);
-                    kap += cr[j] * yj;
-                    g[j] += o[0] * yj;
+                for (int j0 = 0; j0 < NW; j0 += VL) {
+                    const V16 yv = *(const V16 *)(y + j0);
+#pragma unroll
+                    for (int u = 0; u < VL; ++u) {
+                        kap += cr[j0 + u] * yv[u];
+                        g[j0 + u] += o[0] * yv[u];
+                    }
                 }
                 tcx += kap * o[1];
                 tcy += kap * o[2];
@@ -1137,7 +1128,9 @@ hipError_t launch_ecp_pairs(const SysDev &S, const EcpDev &E, const double *R, c
     return hipGetLastError();
 }
 
-static size_t ecp_points_ao_lds(int n) { return sizeof(double) * ((size_t)ECP_AO_ROWS * n + 3 * ECP_AO_ROWS + 256 * 16); }
+static size_t ecp_points_ao_lds(int n, size_t ts) {
+    return std::max(sizeof(double) * 3 * ECP_AO_ROWS + ts * ECP_AO_ROWS * 16 * ((n + 15) / 16), sizeof(double) * 256 * 16);
+}
 static size_t ecp_chain_lds(int N) { return sizeof(double) * ((size_t)7 * N + 256 * 3); }
 
 hipError_t configure_ecp(size_t lds) {
@@ -1175,7 +1168,7 @@ hipError_t launch_ecp_adjoint(const SysDev &S, const EcpDev &E, const T *C, cons
         if (J.MJ > 256 || S.N > 128) return hipErrorInvalidValue;
         hipLaunchKernelGGL((k_ecp_jas<T>), dim3(W), dim3(256), 0, st, S.N, J, R, pos, eb, dedr);
     }
-    const size_t lds = ecp_points_ao_lds(S.n_occ);
+    const size_t lds = ecp_points_ao_lds(S.n_occ, sizeof(T));
     const int nt = (S.n_occ + 15) / 16;
     if (nt == 1)
         hipLaunchKernelGGL((k_ecp_points_ao<T, 1>), dim3(W), dim3(256), lds, st, S, C, R, eb, ktil, G, Gf);

@@ -381,30 +381,6 @@ __device__ inline unsigned long long promote_bits(double x) {
     return (unsigned long long)__double_as_longlong(x > 0.0 ? x : (x <= 0.0 ? 0.0 : __builtin_inf()));
 }
 
-// Exclusive sum of v over the threads of a block of BS and its total: scans
-// within the wavefronts, then over their totals.
-template <int BS>
-__device__ inline int block_excl_scan(int v, int *buf, int &total) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
-    }
-    if (lane == 63) buf[wave] = x;
-    __syncthreads();
-    int before = 0;
-    total = 0;
-#pragma unroll
-    for (int q = 0; q < BS / 64; ++q) {
-        if (q < wave) before += buf[q];
-        total += buf[q];
-    }
-    __syncthreads();
-    return before + x - v;
-}
-
 constexpr int SEL_BS = 1024, SEL_U = 8;   // threads; keys loaded ahead
 
 // Bound: latency of a single block.  A digit is found by a scan over the bins
