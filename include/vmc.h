@@ -439,15 +439,10 @@ int vmc_adjoint(vmc_ctx *ctx, const double *walkers_dev, int64_t n_walkers,
  *   state stays on the device; the host reads it once every 8 iterations.
  *   Several right-hand sides run in lockstep in groups of up to 64, every
  *   read of H shared by the group (an FP64 matrix-core product); each keeps
- *   its own step lengths and stopping test.  Up to 32 right-hand sides
- *   of a large H (one: d of 4000 to about 22000; more: from 2400) that equals
- *   its transpose bit for bit (compared first, one read of H) read its lower
- *   triangle only.  Host output: iters[n_rhs] =
+ *   its own step lengths and stopping test.  Host output: iters[n_rhs] =
  *   iterations used (may be NULL).  Synchronises `stream`; allocates device
  *   scratch for the call: about 4.2 d doubles for one right-hand side,
- *   (3 + s) * g * d doubles for a group of g (s <= 16 column splits); with the
- *   lower triangle (d / 128 + 20) * g * d doubles at most (every element is
- *   read where that cannot be had).
+ *   (3 + s) * g * d doubles for a group of g (s <= 16 column splits).
  * Errors (the first failing right-hand side decides): VMC_EINVAL (NULL
  * pointer, d < 1, n_rhs < 1, rtol <= 0, maxit < 1, unknown flag),
  * VMC_ENOTCONV (maxit reached; z holds the last iterate), VMC_ENONFINITE (a
@@ -468,9 +463,9 @@ int zvector_solve(const double *H_dev, int64_t d, int64_t n_rhs, const double *b
  * hipMalloc).  Same arguments, results and errors as zvector_solve, except
  * that the right-hand sides are solved one after another (no batch shares
  * the reads of H) and d <= ZVECTOR_NOALLOC_MAX_D (VMC_EINVAL beyond).  The
- * CG state (about 4.1 d doubles, with the lower triangle of a symmetric H
- * (d / 256 + 8) d) lives in a library-owned device array of 16 MiB on each
- * GPU, taken on the first call on that GPU and kept until the process ends; it allocates nothing else (no hipMalloc, hipFree or
+ * CG state (about 4.1 d doubles) lives in a library-owned device array of
+ * 2.5 MiB on each GPU, taken on the first call on that GPU and kept until
+ * the process ends; it allocates nothing else (no hipMalloc, hipFree or
  * allocating library call).  All calls on one GPU share that array: calls
  * that overlap in time on one GPU (two host threads, or two streams without
  * synchronisation between them) race and give undefined results.  Every

@@ -594,7 +594,7 @@ static int measure_accumulate(vmc_ctx *c, const double *walkers, int64_t W, cons
 // held until the process ends.  Its name is a host-side stand-in; the device
 // address of each GPU's copy comes from hipGetSymbolAddress, taken once per
 // device with that device current, and only that address is used.
-constexpr int64_t NOALLOC_DOUBLES = vmcx::SYM_ONE_DOUBLES;   // 16 MiB
+constexpr int64_t NOALLOC_DOUBLES = int64_t(5) << 16;   // 2.5 MiB
 static __device__ __align__(256) double scratch[NOALLOC_DOUBLES];
 constexpr int NOALLOC_MAX_DEVICES = 64;
 static std::mutex g_scratch_mu;
@@ -1468,15 +1468,16 @@ static int cg_one(const double *H, int64_t d, const double *b, double *z, double
 }
 
 // Up to 64 CG solves in lockstep, every read of H shared by all of them; each
-// right-hand side keeps its own step lengths and stopping test.  `work` holds
-// cg_batch_bytes.
-static size_t cg_batch_bytes(int64_t d, int nrhs) {
-    return (size_t)(3 + vmcx::cgb_ksplit(d)) * nrhs * d * sizeof(double) + nrhs * sizeof(vmcx::CgState);
-}
-
+// right-hand side keeps its own step lengths and stopping test.
 static int cg_batch(const double *H, int64_t d, int nrhs, const double *b, double *z, double rtol, int32_t maxit,
-                    uint32_t flags, int32_t *iters, void *work, hipStream_t st) {
+                    uint32_t flags, int32_t *iters, hipStream_t st) {
     const size_t vec = (size_t)nrhs * d;
+    const size_t n = 3 * vec + (size_t)vmcx::cgb_ksplit(d) * vec;
+    void *work = nullptr;
+    if (hipMalloc(&work, n * sizeof(double) + nrhs * sizeof(vmcx::CgState)) != hipSuccess) {
+        (void)hipGetLastError();
+        return VMC_ENOMEM;
+    }
     double *R = (double *)work, *P = R + vec, *Dinv = P + vec, *HPp = Dinv + vec;
     vmcx::CgState *cs = (vmcx::CgState *)(HPp + (size_t)vmcx::cgb_ksplit(d) * vec);
     std::vector<vmcx::CgState> hs(nrhs);
@@ -1494,6 +1495,7 @@ static int cg_batch(const double *H, int64_t d, int nrhs, const double *b, doubl
     }
     if (!ok) (void)hipGetLastError();
     (void)hipStreamSynchronize(st);
+    (void)hipFree(work);
     if (!ok) return VMC_EDEVICE;
     int status = VMC_OK;
     for (int k = 0; k < nrhs; ++k) {
@@ -1504,54 +1506,6 @@ static int cg_batch(const double *H, int64_t d, int nrhs, const double *b, doubl
         if (rc != VMC_OK && status == VMC_OK) status = rc;
     }
     return status;
-}
-
-// Up to SYM_RHS CG solves that read the lower triangle of H only, in a
-// workspace of p.doubles.  Returns 1 (and nothing done) where H is not
-// symmetric to the last bit.
-static int cg_symmetric(const vmcx::SymCgPlan &p, const double *H, int64_t d, int nrhs, const double *b, double *z,
-                        double rtol, int32_t maxit, uint32_t flags, int32_t *iters, double *ws, hipStream_t st) {
-    // (the states' two copies and the comparison's result)
-    alignas(16) char raw[2 * vmcx::SYM_RHS * sizeof(vmcx::CgState) + sizeof(int)];
-    const size_t nstate = 2 * nrhs * sizeof(vmcx::CgState);
-    const vmcx::CgState *hs = nullptr;
-    bool ok = vmcx::launch_symcg_setup(p, H, b, d, nrhs, (flags & ZVECTOR_JACOBI) ? 1 : 0, rtol, maxit, ws, st) ==
-              hipSuccess;
-    const int batch = 8;
-    int it = 0, differs = 0;
-    while (ok) {
-        ok = hipMemcpyAsync(raw, ws + p.oC, nstate + sizeof(int), hipMemcpyDeviceToHost, st) == hipSuccess &&
-             hipStreamSynchronize(st) == hipSuccess;
-        if (!ok) break;
-        memcpy(&differs, raw + nstate, sizeof(int));
-        hs = (const vmcx::CgState *)raw + (it & 1) * nrhs;
-        bool all = true;
-        for (int k = 0; k < nrhs; ++k) all = all && hs[k].done;
-        if (differs || all) break;
-        for (int k = 0; ok && k < batch; ++k, ++it)
-            ok = vmcx::launch_symcg_iteration(p, H, d, nrhs, it, ws, st) == hipSuccess;
-    }
-    if (ok && !differs) ok = vmcx::launch_symcg_out(p, ws, d, nrhs, z, st) == hipSuccess;
-    if (!ok) (void)hipGetLastError();
-    (void)hipStreamSynchronize(st);
-    if (!ok) return VMC_EDEVICE;
-    if (differs) return 1;
-    int status = VMC_OK;
-    for (int k = 0; k < nrhs; ++k) {
-        if (iters) iters[k] = hs[k].it;
-        const int rc = hs[k].done == vmcx::CG_NONFINITE ? VMC_ENONFINITE
-                       : hs[k].done == vmcx::CG_CONVERGED ? VMC_OK
-                                                          : VMC_ENOTCONV;
-        if (rc != VMC_OK && status == VMC_OK) status = rc;
-    }
-    return status;
-}
-
-// Bytes of the workspace of one group of solves that read every element of H.
-static size_t zvector_full_bytes(int64_t d, int64_t n_rhs) {
-    // one right-hand side: r, p, Hp, dinv, the matvec partials, then the iteration state
-    return n_rhs > 1 ? cg_batch_bytes(d, (int)std::min<int64_t>(64, n_rhs))
-                     : (4 * (size_t)d + (size_t)vmcx::cg_matvec_blocks(d)) * sizeof(double) + sizeof(vmcx::CgState);
 }
 
 int zvector_solve(const double *H, int64_t d, int64_t n_rhs, const double *b, double *z, double rtol, int32_t maxit,
@@ -1561,41 +1515,32 @@ int zvector_solve(const double *H, int64_t d, int64_t n_rhs, const double *b, do
     if (iters)
         for (int64_t k = 0; k < n_rhs; ++k) iters[k] = 0;
     hipStream_t st = (hipStream_t)stream;
-    const size_t full = zvector_full_bytes(d, n_rhs);
-    void *work = nullptr;
-    vmcx::SymCgPlan p{};
-    if (n_rhs <= vmcx::SYM_RHS) p = vmcx::symcg_plan(d, (int)n_rhs);
-    if (p.doubles) {
-        // one workspace for both ways (a second allocation cost up to 0.7 ms
-        // where H turned out not to be symmetric)
-        if (hipMalloc(&work, std::max(full, (size_t)p.doubles * sizeof(double))) == hipSuccess) {
-            const int rc = cg_symmetric(p, H, d, (int)n_rhs, b, z, rtol, maxit, flags, iters, (double *)work, st);
-            if (rc != 1) {
-                (void)hipFree(work);
-                return rc;
-            }
-        } else {
-            (void)hipGetLastError();
-            work = nullptr;
-        }
-    }
-    if (!work && hipMalloc(&work, full) != hipSuccess) {
-        (void)hipGetLastError();
-        return VMC_ENOMEM;
-    }
-    // every element of H read: any H, any d, any number
-    int status = VMC_OK;
-    if (n_rhs == 1) {
-        status = cg_one(H, d, b, z, rtol, maxit, flags, iters, (double *)work, st);
-    } else {
+    if (n_rhs > 1) {
         // groups of up to 64 right-hand sides share the reads of H
+        int status = VMC_OK;
         for (int64_t k0 = 0; k0 < n_rhs; k0 += 64) {
             const int g = (int)std::min<int64_t>(64, n_rhs - k0);
             const int rc = cg_batch(H, d, g, b + k0 * d, z + k0 * d, rtol, maxit, flags, iters ? iters + k0 : nullptr,
-                                    work, st);
+                                    st);
             if (rc != VMC_OK && status == VMC_OK) status = rc;
-            if (rc == VMC_EDEVICE) break;
+            if (rc == VMC_EDEVICE || rc == VMC_ENOMEM) break;
         }
+        return status;
+    }
+    // r, p, Hp, dinv, the matvec partials, then the iteration state
+    const size_t nwork = 4 * (size_t)d + (size_t)vmcx::cg_matvec_blocks(d);
+    void *work = nullptr;
+    if (hipMalloc(&work, nwork * sizeof(double) + sizeof(vmcx::CgState)) != hipSuccess) {
+        (void)hipGetLastError();
+        return VMC_ENOMEM;
+    }
+    int status = VMC_OK;
+    for (int64_t k = 0; k < n_rhs; ++k) {
+        const int rc = cg_one(H, d, b + k * d, z + k * d, rtol, maxit, flags, iters ? iters + k : nullptr,
+                              (double *)work, st);
+        // the first failure decides the status; a device error stops at once
+        if (rc != VMC_OK && status == VMC_OK) status = rc;
+        if (rc == VMC_EDEVICE) break;
     }
     (void)hipStreamSynchronize(st);
     (void)hipFree(work);
@@ -1618,15 +1563,8 @@ int zvector_solve_noalloc(const double *H, int64_t d, int64_t n_rhs, const doubl
     // every scratch value is written by the setup kernel before it is read,
     // so what the last call left there does not matter
     int status = VMC_OK;
-    const vmcx::SymCgPlan p = vmcx::symcg_plan(d, 1);
-    bool sym = p.doubles != 0;   // until H turns out not to be
     for (int64_t k = 0; k < n_rhs; ++k) {
-        int32_t *itk = iters ? iters + k : nullptr;
-        int rc = sym ? cg_symmetric(p, H, d, 1, b + k * d, z + k * d, rtol, maxit, flags, itk, work, st) : 1;
-        if (rc == 1) {
-            sym = false;
-            rc = cg_one(H, d, b + k * d, z + k * d, rtol, maxit, flags, itk, work, st);
-        }
+        const int rc = cg_one(H, d, b + k * d, z + k * d, rtol, maxit, flags, iters ? iters + k : nullptr, work, st);
         if (rc != VMC_OK && status == VMC_OK) status = rc;
         if (rc == VMC_EDEVICE) break;
     }

@@ -81,27 +81,6 @@ hipError_t launch_cgb_iteration(const double *H, int64_t d, int nrhs, double *X,
                                 const double *dinv, CgState *cs, hipStream_t st);
 hipError_t launch_cg_iteration(const double *H, int64_t d, double *x, double *r, double *p, double *Hp,
                                const double *dinv, double *part, CgState *cs, hipStream_t st);
-// Conjugate gradients that read the lower triangle of a symmetric H only, n <=
-// 32 right-hand sides in lockstep (vmc_symcg.hip): the layout of the workspace
-// (offsets in doubles; doubles = 0: d and n for which the calls above are used).
-// The setup also compares H with its transpose (bit for bit) and leaves nonzero
-// in the int after the 2 n states where they differ; iteration it reads the
-// states' copy it & 1 and writes the other.  One right-hand side is solved so
-// only within SYM_ONE_DOUBLES of workspace (d up to 22000): the scratch of the
-// allocation-free entry point, which gives the same bits.
-constexpr int64_t SYM_ONE_DOUBLES = int64_t(1) << 21;
-constexpr int SYM_RHS = 32;
-struct SymCgPlan {
-    int tb, G, slots;
-    int64_t units, blocks, doubles;
-    int64_t oP, oR, oX, oD, oY, oH, oS, oC;
-};
-SymCgPlan symcg_plan(int64_t d, int n);
-hipError_t launch_symcg_setup(const SymCgPlan &p, const double *H, const double *b, int64_t d, int n, int jacobi,
-                              double rtol, int maxit, double *ws, hipStream_t st);
-hipError_t launch_symcg_iteration(const SymCgPlan &p, const double *H, int64_t d, int n, int it, double *ws,
-                                  hipStream_t st);
-hipError_t launch_symcg_out(const SymCgPlan &p, const double *ws, int64_t d, int n, double *z, hipStream_t st);
 hipError_t launch_zv_rhs(const double *Cv, const double *G, int64_t M, int64_t nv, int64_t n, int64_t nbat,
                          double *b, hipStream_t st);
 hipError_t launch_zv_backmap(const double *Cv, const double *z, int64_t M, int64_t nv, int64_t n, int64_t nbat,

@@ -630,41 +630,30 @@ __global__ __launch_bounds__(CG_BS) void k_cgb_update(double *__restrict__ X, do
     }
 }
 
-// out[r][i] = sum_k A_kr X[k][i], k < K, r < rows, i < n: the right-hand side
-// b = Cv^T G (TR: A_kr = Cv[k][r], the virtual-occupied block of C^T G) and the
-// back-map Z = Cv z (A_kr = Cv[r][k]).  A block takes 64 outputs, each of its
-// wavefronts a quarter of the k; eight k in flight.  Latency bound: at 47 x 188
-// rotations of 235 AOs a thread that walks all k took 70 and 48 us, this takes
-// 7 and 7 (a batch of 12: 84 and 51, 28 and 27).
-template <bool TR>
-__global__ __launch_bounds__(256) void k_zv_product(const double *__restrict__ Cv, const double *__restrict__ X,
-                                                    int64_t nv, int64_t K, int64_t rows, int64_t n,
-                                                    double *__restrict__ out) {
-    __shared__ double part[4][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    X += (size_t)blockIdx.y * K * n;   // batch item
-    out += (size_t)blockIdx.y * rows * n;
-    const int64_t o = (int64_t)blockIdx.x * 64 + lane, oc = min(o, rows * n - 1), r = oc / n, i = oc % n;
-    const int64_t k0 = K * wave / 4, k1 = K * (wave + 1) / 4;
-    const double *a = TR ? Cv + r : Cv + r * nv;
-    const int64_t da = TR ? nv : 1;
+// b[a][i] = sum_mu Cv[mu][a] G[mu][i] (the virtual-occupied block of C^T G)
+__global__ void k_zv_rhs(const double *__restrict__ Cv, const double *__restrict__ G, int64_t M, int64_t nv,
+                         int64_t n, double *__restrict__ b) {
+    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    G += (size_t)blockIdx.y * M * n;   // batch item
+    b += (size_t)blockIdx.y * nv * n;
+    if (o >= nv * n) return;
+    const int64_t a = o / n, i = o % n;
     double s = 0.0;
-    int64_t k = k0;
-    for (; k + 8 <= k1; k += 8) {
-        double av[8], xv[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            av[u] = a[(k + u) * da];
-            xv[u] = X[(k + u) * n + i];
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) s = fma(av[u], xv[u], s);
-    }
-    for (; k < k1; ++k) s = fma(a[k * da], X[k * n + i], s);
-    part[wave][lane] = s;
-    __syncthreads();
-    if (wave == 0 && o < rows * n)
-        out[o] = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
+    for (int64_t mu = 0; mu < M; ++mu) s = fma(Cv[mu * nv + a], G[mu * n + i], s);
+    b[o] = s;
+}
+
+// Z[mu][i] = sum_a Cv[mu][a] z[a][i]
+__global__ void k_zv_backmap(const double *__restrict__ Cv, const double *__restrict__ z, int64_t M, int64_t nv,
+                             int64_t n, double *__restrict__ Z) {
+    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    z += (size_t)blockIdx.y * nv * n;   // batch item
+    Z += (size_t)blockIdx.y * M * n;
+    if (o >= M * n) return;
+    const int64_t mu = o / n, i = o % n;
+    double s = 0.0;
+    for (int64_t a = 0; a < nv; ++a) s = fma(Cv[mu * nv + a], z[a * n + i], s);
+    Z[o] = s;
 }
 
 // ---------------------------------------------------------------------------
@@ -776,15 +765,15 @@ hipError_t launch_cg_iteration(const double *H, int64_t d, double *x, double *r,
 
 hipError_t launch_zv_rhs(const double *Cv, const double *G, int64_t M, int64_t nv, int64_t n, int64_t nbat,
                          double *b, hipStream_t st) {
-    hipLaunchKernelGGL(k_zv_product<true>, dim3((unsigned)((nv * n + 63) / 64), (unsigned)nbat), dim3(256), 0, st, Cv,
-                       G, nv, M, nv, n, b);
+    hipLaunchKernelGGL(k_zv_rhs, dim3((unsigned)((nv * n + 255) / 256), (unsigned)nbat), dim3(256), 0, st, Cv, G, M,
+                       nv, n, b);
     return hipGetLastError();
 }
 
 hipError_t launch_zv_backmap(const double *Cv, const double *z, int64_t M, int64_t nv, int64_t n, int64_t nbat,
                              double *Z, hipStream_t st) {
-    hipLaunchKernelGGL(k_zv_product<false>, dim3((unsigned)((M * n + 63) / 64), (unsigned)nbat), dim3(256), 0, st, Cv,
-                       z, nv, nv, M, n, Z);
+    hipLaunchKernelGGL(k_zv_backmap, dim3((unsigned)((M * n + 255) / 256), (unsigned)nbat), dim3(256), 0, st, Cv, z,
+                       M, nv, n, Z);
     return hipGetLastError();
 }
 
