@@ -492,7 +492,10 @@ __global__ __launch_bounds__(CG_BS) void k_cg_update(double *__restrict__ x, dou
 // right-hand sides' 32 columns in LDS, each wavefront accumulates 16 rows x
 // 16*NRT right-hand sides, and the columns are split over ksplit blocks whose
 // partial products the update kernel adds in a fixed order.  The per-RHS
-// vector work runs one block per right-hand side.
+// vector work runs one block per right-hand side.  Bound: HBM (12 right-hand
+// sides at d = 8836: 135 us, 4.6 TB/s; 247 while every load formed and clamped
+// its own 64-bit address, as much vector work as the products).  The order of
+// each sum is part of the result: it decides the last iteration.
 // ---------------------------------------------------------------------------
 constexpr int CGB_ROWS = 64;          // rows of H per block (16 per wavefront)
 constexpr int CGB_KC = 32;            // columns per LDS stage
@@ -521,22 +524,29 @@ __global__ __launch_bounds__(256) void k_cgb_matvec(const double *__restrict__ H
     // stage st+1 is loaded into registers while stage st is multiplied
     constexpr int HQ = CGB_ROWS * CGB_KC / 256, PQ = 16 * NRT * CGB_KC / 256;
     double hr[HQ], pr[PQ];
+    // (a uniform base and one 32-bit offset per load; rows past d read row
+    // d - 1, whose products are not stored, and right-hand sides past nrhs the
+    // last; in the last, partial stage the columns past d are replaced by 0)
+    const int cc = tid % CGB_KC, rr = tid / CGB_KC;
+    unsigned ho[HQ], po[PQ];
+#pragma unroll
+    for (int q = 0; q < HQ; ++q) ho[q] = (unsigned)min((int64_t)(rr + 8 * q), d - 1 - r0) * (unsigned)d + cc;
+#pragma unroll
+    for (int q = 0; q < PQ; ++q) po[q] = (unsigned)min(rr + 8 * q, nrhs - 1) * (unsigned)d + cc;
+    const double *H0 = H + r0 * d;
     auto load = [&](int64_t st) {
         const int64_t c0 = st * CGB_KC;
-        // clamped, unconditional loads (selected afterwards)
+        const double *hs = H0 + c0, *ps = P + c0;
+        const unsigned over = (unsigned)max((int64_t)0, c0 + cc - (d - 1));   // columns past the last
 #pragma unroll
-        for (int q = 0; q < HQ; ++q) {
-            const int i = tid + 256 * q, rr = i / CGB_KC, cc = i % CGB_KC;
-            const int64_t row = r0 + rr, col = c0 + cc;
-            const double v = H[min(row, d - 1) * d + min(col, d - 1)];
-            hr[q] = (row < d && col < d) ? v : 0.0;
-        }
+        for (int q = 0; q < HQ; ++q) hr[q] = hs[ho[q] - over];
 #pragma unroll
-        for (int q = 0; q < PQ; ++q) {
-            const int i = tid + 256 * q, kk = i / CGB_KC, cc = i % CGB_KC;
-            const int64_t col = c0 + cc;
-            const double v = P[(int64_t)min(kk, nrhs - 1) * d + min(col, d - 1)];
-            pr[q] = (kk < nrhs && col < d) ? v : 0.0;
+        for (int q = 0; q < PQ; ++q) pr[q] = ps[po[q] - over];
+        if (c0 + CGB_KC > d && over) {
+#pragma unroll
+            for (int q = 0; q < HQ; ++q) hr[q] = 0.0;
+#pragma unroll
+            for (int q = 0; q < PQ; ++q) pr[q] = 0.0;
         }
     };
     if (s0 < s1) load(s0);
