@@ -491,6 +491,10 @@ hipError_t launch_dense(const SysDev &S, const double *R, const MeasBufs<T> &mb,
                         const DenseLayout &L, int W, hipStream_t st) {
     const int kn = sweep_kn(S.n_occ);
     const bool state = mb.kst != nullptr;
+    // Where one inverse is held at a time, the second block's replaces the
+    // first's behind the barriers of the Abar part only: a block without that
+    // part would overwrite an inverse that other wavefronts still read.
+    if (state && kn >= 48 && !mb.ktil && !mb.promote_key) return hipErrorInvalidValue;
     const dim3 g((unsigned)W), b((unsigned)(64 * dense_waves(kn)));
 #define DENSE(KN)                                                                                                     \
     case KN:                                                                                                          \
