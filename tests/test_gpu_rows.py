@@ -67,3 +67,24 @@ def test_many_rows(dev, extra):
     vmc.Context(m, max_walkers=W, precision="mixed").sweep(w, 2, 5, measure=False)
     vmc.Context(m, max_walkers=W, precision="mixed").sweep(part, 2, 5, measure=False)
     assert torch.equal(w[:few], part)
+
+
+@pytest.mark.parametrize("n", [17, 32, 33, 48, 49, 64])
+def test_many_rows_orbital_classes(dev, n):
+    """The same at the edges of the other classes of 16 orbitals (each its own
+    instance of both kernels): just over 2^20 rows, identical chains."""
+    from paper_2511_05222_amd import vmc
+    m = dataclasses.replace(inputs.family_member(6).molecule, n_up=n, n_dn=n)
+    N, few = 2 * n, 501
+    W = -(-(1 << 20) // N) + 1
+    g = torch.Generator(device=dev)
+    g.manual_seed(n)
+    at = torch.tensor(m.xyz[np.arange(N) % m.n_atoms], device=dev)
+    w = (at + 0.5 * torch.randn((W, N, 3), dtype=torch.float64, device=dev, generator=g)).contiguous()
+    assert few * N < (1 << 20) <= W * N
+    start, part = w[:few].clone(), w[:few].clone()
+    ctx = vmc.Context(m, max_walkers=W, precision="mixed")
+    ctx.sweep(w, 1, 5, measure=False)
+    ctx.sweep(part, 1, 5, measure=False)
+    assert not torch.equal(part, start)
+    assert torch.equal(w[:few], part)
