@@ -52,3 +52,23 @@ def test_state_against_rows(dev, n, refresh, prec, tol):
     for k in ("E", "F_bare", "dE_dC", "dEL_dC_mean"):
         x, y = np.asarray(a[k]), np.asarray(b[k])
         assert np.abs(x - y).max() <= tol * max(np.abs(y).max(), 1e-300), k
+
+
+@pytest.mark.parametrize("n", [15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64])
+def test_newton_step_corrects_the_sweep_inverse(dev, n):
+    """The energy from the sweep's FP32 inverses against that from the MO rows
+    alone.  Both take the same FP32 orbital values and sum in FP64, so what is
+    left is the inverse: R = I - A K is 2e-5 .. 2e-3 after a sweep of FP32
+    updates and shifts the energy by 9e-9 .. 1e-5 of itself; one FP64 step
+    leaves R^2, at most 7e-11 (all from an emulation of such a sweep on the
+    host)."""
+    from paper_2511_05222_amd import vmc
+    m = molecule(n)
+    ctx = vmc.Context(m, max_walkers=7, precision="mixed", refresh_period=4 * n + 1, promote_fraction=0.0)
+    w = torch.tensor(inputs.initial_walkers(m, 7, 6), device=dev)
+    ctx.sweep(w, 2, 9, measure=False)
+    ctx.sweep(w, 1, 9, sweep_offset=2, measure=True)
+    a = ctx.accumulate()["E"]
+    ctx.accumulate_walkers(w)
+    b = ctx.accumulate()["E"]
+    assert abs(a - b) <= 1e-9 * max(abs(b), 10.0), (a, b)
