@@ -21,11 +21,12 @@
 // the evaluations; FP64 34 % and 41 %, the rest latency that two wavefronts a
 // SIMD do not hide.
 //   FP64: an AO's lane used to form its shell's radial sums itself, each
-// shell's 2.3 times over with exponents read from memory; now eight lanes a
-// shell form them once (SHARED), in LDS until the AOs' lanes read them.  With
-// shorter algebra for t_k and one LDS update per sum (below): 235 AOs, 94
-// electrons, 16384 walkers 7.71 -> 6.93 ms, 75 AOs, 26 electrons 1.17 -> 0.66
-// (there also from four wavefronts a block for 5 sub-tiles), H2 30 -> 11 us.
+// shell's 2.3 times over with exponents read from memory; now four or eight
+// lanes a shell form them once (SHARED), in LDS until the AOs' lanes read them.
+// With shorter algebra for t_k and one LDS update per sum (below): 235 AOs, 94
+// electrons, 8192 walkers 3.87 -> 3.42 ms; 75 AOs, 26 electrons, 16384 walkers
+// 1.17 -> 0.66 (there also from four wavefronts a block for 5 sub-tiles); H2 30
+// -> 11 us.
 //   FP32: radial sums are cheap and in registers; shared they cost more in
 // LDS round trips than they save (6.50 against 6.08 ms, 235 AOs, 32768
 // walkers).
@@ -192,15 +193,20 @@ void k_adjoint_mfma(SysDev S, const T *__restrict__ C, const double *__restrict_
     // order of their sum is the same in every block.
     const int share = nw == 8 ? (wave + (w >> 3) + (w >> 8)) & 7 : wave;
     double *dw = dpw + share * dst;
-    V4 *xr = (V4 *)(dpw + nw * dst) + wave * 8 * ADJ_XS;   // radial sums, [8 electrons][ADJ_XS shells]
+    V4 *xr = (V4 *)(dpw + nw * dst) + wave * 8 * ADJ_XS;   // radial sums, [4 VU electrons][XS shells]
     const int ml = lane & 15, kg = lane >> 4;
-    // evaluations a turn, and the dE_L/dr sum this lane gets of a turn's
-    // (two where the registers allow it: fewer lane moves a sum)
-    constexpr int VU = sizeof(T) == 8 || NT == 3 ? 2 : 1;
+    // Evaluations a turn, and the dE_L/dr sum this lane gets of a turn's: two
+    // take fewer lane moves a sum, one fewer registers.  Two / one, 4096 walkers:
+    // FP32 with 20, 32, 37 and 47 orbitals 200 / 203, 369 / 387, 539 / 552 and
+    // 808 / 823 us, with 13 and 56 (both spill) 123 / 94 and 1318 / 1238; FP64
+    // with 13 and 32 171 / 198 and 650 / 705, with 37, 47, 56 and 64 (all spill)
+    // 1072 / 1025, 1770 / 1717, 2605 / 2400 and 3003 / 2700.
+    constexpr int VU = sizeof(T) == 8 ? (NT <= 2 ? 2 : 1) : (NT == 2 || NT == 3 ? 2 : 1);
     const int dq = row16_which<3 * VU>(ml), de = MF::row(lane, dq / 3), dc = dq % 3;
     const bool dmine = VU == 2 ? (ml & 8) == 0 && (ml & 6) != 6 : ml < 3;
-    // the electron (of 8) and shell of this lane in the radial phase
-    const int ri = lane & 7, rj = lane >> 3, re = MF::row(16 * (ri >> 1), ri & 1);
+    // the electron (of 4 VU) and shell (of XS) of this lane in the radial phase
+    constexpr int XS = 2 * ADJ_XS / VU;
+    const int ri = lane % (4 * VU), rj = lane / (4 * VU), re = MF::row(16 * (ri / VU), ri % VU);
     const int n_sub = (M + 15) >> 4;
     for (int st = share; st < n_sub; st += nw) {
         const int mu = 16 * st + ml;
@@ -244,23 +250,26 @@ void k_adjoint_mfma(SysDev S, const T *__restrict__ C, const double *__restrict_
             // reaches a sum.
 #pragma unroll 1
             for (int h = 0; h < 4; h += VU) {
-                V4 rs[2];
+                V4 rs[VU];
                 if (SHARED) {
-                    // radial sums of the sub-tile's shells, ADJ_XS at a time, at
-                    // the turn's 8 electrons, then to the lanes of their AOs
+                    // radial sums of the sub-tile's shells, XS at a time, at the
+                    // turn's electrons, then to the lanes of their AOs
                     const int ec = min(16 * rt + MF::row(0, h) + re, N - 1);
                     const double px = sp[3 * ec], py = sp[3 * ec + 1], pz = sp[3 * ec + 2];
-                    for (int q = 0; q < ns; q += ADJ_XS) {
-                        if (ns > ADJ_XS) shell_lane_load<T>(S, R, s0 + min(q + rj, ns - 1), sl);
+                    for (int q = 0; q < ns; q += XS) {
+                        if (ns > XS) shell_lane_load<T>(S, R, s0 + min(q + rj, ns - 1), sl);
                         const double dx = px - sl.x, dy = py - sl.y, dz = pz - sl.z;
                         T o[4];
                         shell_lane_radial<T>(sl, S.basis, dx * dx + dy * dy + dz * dz, o);
                         wave_sync_s();
-                        if (rj < ADJ_XS) xr[ADJ_XS * ri + rj] = V4{o[0], o[1], o[2], o[3]};
+                        if (rj < XS) xr[XS * ri + rj] = V4{o[0], o[1], o[2], o[3]};
                         wave_sync_s();
-                        const int j = max(0, min(sj - q, ADJ_XS - 1));
-                        const V4 r0 = xr[2 * ADJ_XS * kg + j], r1 = xr[2 * ADJ_XS * kg + ADJ_XS + j];
-                        if (sj >= q) rs[0] = r0, rs[1] = r1;
+                        const V4 *r = xr + XS * VU * kg + max(0, min(sj - q, XS - 1));
+#pragma unroll
+                        for (int v = 0; v < VU; ++v) {
+                            const V4 x = r[XS * v];
+                            if (sj >= q) rs[v] = x;
+                        }
                     }
                 }
                 T t[3 * VU];

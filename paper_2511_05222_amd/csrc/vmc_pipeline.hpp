@@ -38,8 +38,9 @@ struct DenseLayout {
     size_t bytes, bytes_one;   // both spin blocks' inverses, one of them
 };
 
-// Shells of k_adjoint_mfma's shared radial sums at a time (odd: no bank
-// conflicts; a sub-tile of 16 AOs mostly holds parts of 7 shells)
+// Shells of k_adjoint_mfma's shared radial sums at a time, at eight electrons
+// (odd: no bank conflicts; a sub-tile of 16 AOs mostly holds parts of 7 shells)
+// or twice as many at four
 constexpr int ADJ_XS = 7;
 
 // LDS layout of k_adjoint_mfma (bytes).

@@ -67,3 +67,20 @@ def test_many_walkers(dev, n, prec):
     many, parts = ctx.measure(w), [ctx.measure(x.contiguous()) for x in (w[:500], w[500:512], w[512:])]
     for k in many:
         assert torch.equal(many[k], torch.cat([p[k] for p in parts])), k
+
+
+@pytest.mark.parametrize("n,ls", [(32, (0,)), (33, (0,)), (48, (0,)), (49, (0,)), (56, (0,)), (40, (0, 0, 0, 1)),
+                                  (50, (0,) * 13 + (1,)), (56, (0, 0, 1))])
+def test_subtiles_of_many_shells(dev, n, ls):
+    """FP64 takes 7 shells at a time, from 33 orbitals on 14: sub-tiles of 16,
+    14 and fewer.  (FP64 only: FP32 shares no sums, and some of these bases
+    give Slater blocks of condition 2e5.)"""
+    from oracle import derivatives as dv, wavefunction as wf
+    from paper_2511_05222_amd import vmc
+    m = molecule(n, ls)
+    r = inputs.initial_walkers(m, 3, 3)
+    ref = dv.measure(wf.System(m), m.xyz, r)
+    out = vmc.Context(m, max_walkers=3).measure(torch.tensor(r, device=dev))
+    for a, b in (("dEL_dR", "H"), ("O", "O"), ("G", "G")):
+        err = np.abs(out[a].cpu().numpy() - ref[b]).max() / np.abs(ref[b]).max()
+        assert err <= 1e-10, (a, err)
