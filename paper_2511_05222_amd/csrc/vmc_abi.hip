@@ -300,8 +300,9 @@ static void layouts(vmc_ctx *c) {
     d.off_p = 0;
     d.off_g = d.off_p + al((size_t)3 * N * 8);
     d.off_x = d.off_g + al((size_t)3 * N * 8);
-    // (X's place first holds the pair tables)
-    const int nw = vmcx::dense_waves(kn), ng = 64 * nw / vmcx::dense_pair_lanes(kn);
+    // (X's place first holds the pair tables; a launch with fewer wavefronts
+    // needs fewer)
+    const int nw = vmcx::dense_waves(kn, false), ng = 64 * nw / vmcx::dense_pair_lanes(kn);
     d.off_perm = d.off_x + al((size_t)std::max(kn * d.ldk, (ng + std::max(ng, nw)) * 3 * N) * 8);
     d.off_red = d.off_perm + al(128 * 4);
     d.off_k = d.off_red + al(24 * 8);

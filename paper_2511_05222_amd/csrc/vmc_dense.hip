@@ -1,6 +1,7 @@
 // vmc_dense.hip -- per-walker dense part of one measurement (gfx950).
 //
-// One block of four wavefronts (eight from 49 orbitals on) per walker.
+// One block of four wavefronts per walker (eight from 49 orbitals on where both
+// inverses are held).
 //   phase A  waves 0 and 1: the inverse K of the up and down Slater blocks by
 //            in-register Gauss-Jordan (FP64, partial pivoting), log|det|; or,
 //            after a sweep, the sweep's inverse of the block followed by one
@@ -72,9 +73,9 @@ __device__ inline double block_sum(double v, double *red) {
 // (two of 64 orbitals) fit on a CU; otherwise wavefronts 0 and 1 load or form
 // both at the start.
 template <typename T, int KN, bool STATE>
-__global__ __launch_bounds__(64 * dense_waves(KN)) __attribute__((amdgpu_waves_per_eu(STATE && KN == 48 ? 3 : 2)))
+__global__ __launch_bounds__(64 * dense_waves(KN, STATE)) __attribute__((amdgpu_waves_per_eu(STATE && KN == 48 ? 3 : 2)))
 void k_dense(SysDev S, const double *__restrict__ R, MeasBufs<T> mb, WalkerOut out, int *status, DenseLayout L) {
-    constexpr int NW = dense_waves(KN), NT = 64 * NW;   // wavefronts, threads
+    constexpr int NW = dense_waves(KN, STATE), NT = 64 * NW;   // wavefronts, threads
     constexpr int GL = dense_pair_lanes(KN), NG = NT / GL, NTAB = NG > NW ? NG : NW;
     typedef Mfma<double> MF;
     constexpr int RTS = KN / 16;                    // 16-row tiles of a spin block
@@ -495,7 +496,7 @@ hipError_t launch_dense(const SysDev &S, const double *R, const MeasBufs<T> &mb,
     // first's behind the barriers of the Abar part only: a block without that
     // part would overwrite an inverse that other wavefronts still read.
     if (state && kn >= 48 && !mb.ktil && !mb.promote_key) return hipErrorInvalidValue;
-    const dim3 g((unsigned)W), b((unsigned)(64 * dense_waves(kn)));
+    const dim3 g((unsigned)W), b((unsigned)(64 * dense_waves(kn, state)));
 #define DENSE(KN)                                                                                                     \
     case KN:                                                                                                          \
         if (state)                                                                                                    \

@@ -26,12 +26,16 @@ struct SweepLayout {
     size_t bytes;                                   // per block
 };
 
-// LDS layout of k_dense (bytes).
 // k_dense's blocks for spin blocks of up to kn orbitals: wavefronts, and lanes
-// of a group that takes a round of electron pairs (at least 2 kn electrons)
-constexpr int dense_waves(int kn) { return kn == 64 ? 8 : 4; }
+// of a group that takes a round of electron pairs (at least 2 kn electrons).
+// With 64 orbitals and both inverses in LDS one block fits on a CU, which eight
+// wavefronts fill; where one inverse at a time is held (state), two blocks of
+// four fit (56 orbitals, 8192 walkers FP32, four / eight: both inverses 2.58 /
+// 2.19 ms, one 1.58 / 2.14).
+constexpr int dense_waves(int kn, bool state) { return kn == 64 && !state ? 8 : 4; }
 constexpr int dense_pair_lanes(int kn) { return kn == 16 ? 32 : (kn == 32 ? 64 : 128); }
 
+// LDS layout of k_dense (bytes).
 struct DenseLayout {
     int ldk;                 // row stride (doubles, odd) of K, X and T
     int off_p, off_g, off_x, off_perm, off_red, off_k;
