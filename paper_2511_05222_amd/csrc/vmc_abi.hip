@@ -759,20 +759,29 @@ static int prepare(vmc_ctx *c, Prepared &P, const double *C, const double *R, hi
     return VMC_OK;
 }
 
-// The buffers of a Prepared, sharing t's tile headers.
-static int alloc_prepared(vmc_ctx *c, Prepared &P, bool mixed) {
-    double *Cp = nullptr;
-    float *Cpf = nullptr, *Cf = nullptr;
-    ShellRec *rec = nullptr;
-    const size_t np = (size_t)(c->M + 16) * 64;
-    int rc;
-    if ((rc = c->dalloc(&Cp, np)) || (rc = c->dalloc(&rec, c->h_rec.size()))) return rc;
-    if (mixed && ((rc = c->dalloc(&Cpf, np)) || (rc = c->dalloc(&Cf, (size_t)c->M * c->n_occ)))) return rc;
-    P = c->own;
-    P.Cp = Cp;
-    P.Cpf = Cpf;
-    P.Cf = Cf;
-    P.mo.rec = P.j16.rec = P.j32.rec = rec;   // (a tile's first record counts from the common base)
+// The buffers of both Prepared (which share the tile headers) and the records
+// without positions, in one allocation (as up to nine they took 20 to 50 us more
+// of vmc_init).
+static int alloc_prepared(vmc_ctx *c, bool mixed) {
+    const size_t nr = c->h_rec.size() * sizeof(ShellRec), np = (size_t)(c->M + 16) * 64;
+    const size_t nf = mixed ? (size_t)c->M * c->n_occ : 0;
+    // a set: records, C padded in FP64 and FP32, C in FP32
+    const size_t off_p = nr, off_pf = off_p + np * 8, off_f = off_pf + (mixed ? np * 4 : 0);
+    const size_t set = (off_f + nf * 4 + 127) & ~(size_t)127;
+    unsigned char *buf = nullptr;
+    if (const int rc = c->dalloc(&buf, 2 * set + nr)) return rc;
+    c->d_rec = (ShellRec *)(buf + 2 * set);
+    HIP_OK(c, hipMemcpy(c->d_rec, c->h_rec.data(), nr, hipMemcpyHostToDevice));
+    c->user = c->own;
+    for (Prepared *P : {&c->own, &c->user}) {
+        P->Cp = (double *)(buf + off_p);
+        if (mixed) {
+            P->Cpf = (float *)(buf + off_pf);
+            P->Cf = (float *)(buf + off_f);
+        }
+        P->mo.rec = P->j16.rec = P->j32.rec = (ShellRec *)buf;   // (a tile's first record counts from the common base)
+        buf += set;
+    }
     return VMC_OK;
 }
 
@@ -1023,13 +1032,8 @@ int vmc_init(const vmc_basis *basis, const vmc_nuclei *nuclei, const vmc_mo *mo,
     if (c->MJ > 0 && (rc = setup_body_jastrow(c, jas, A))) return bail(rc);
     if (opt->ecp && (rc = setup_ecp(c, opt->ecp, A))) return bail(rc);
     c->h_rec.push_back(ShellRec{});   // (the row kernels load one record ahead)
-    if ((rc = c->upload(&c->d_rec, c->h_rec.data(), c->h_rec.size())) ||
-        (rc = alloc_prepared(c, c->user, opt->precision == VMC_MIXED)) ||
-        (rc = alloc_prepared(c, c->own, opt->precision == VMC_MIXED)) ||
-        (rc = prepare(c, c->own, c->d_C, c->d_R, nullptr)))
+    if ((rc = alloc_prepared(c, opt->precision == VMC_MIXED)) || (rc = prepare(c, c->own, c->d_C, c->d_R, nullptr)))
         return bail(rc);
-    // (the calls may come on streams that do not wait for the default one)
-    if (hipStreamSynchronize(nullptr) != hipSuccess) return bail(c->fail(VMC_EDEVICE, "hipStreamSynchronize failed"));
 
     SysDev &sd = c->sys;
     sd.N = c->N;
@@ -1190,6 +1194,9 @@ int vmc_init(const vmc_basis *basis, const vmc_nuclei *nuclei, const vmc_mo *mo,
         hipMemset(c->status, 0, 4) != hipSuccess || hipMemset(c->blocks, 0, MAX_BLOCKS * 8) != hipSuccess ||
         hipMemset(c->blocks_w, 0, MAX_BLOCKS * 8) != hipSuccess)
         return bail(c->fail(VMC_EDEVICE, "hipMemset failed"));
+    // (k_prepare: the calls may come on streams that do not wait for the default
+    // one; it has run beside the allocations)
+    if (hipStreamSynchronize(nullptr) != hipSuccess) return bail(c->fail(VMC_EDEVICE, "hipStreamSynchronize failed"));
     *out = c;
     return VMC_OK;
 }
