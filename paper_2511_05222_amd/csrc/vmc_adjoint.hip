@@ -36,17 +36,14 @@
 
 namespace vmcx {
 
-// The shell of one lane of the radial phase.
-template <typename T>
+// The shell of one lane of the radial phase (FP64).
 struct ShellLane {
     static constexpr int NP = 3;   // primitives held in registers
-    double x, y, z, alt[NP];       // alt = al log2(e) (FP32 exponential)
-    T al[NP], cp[NP];
+    double x, y, z, al[NP], cp[NP];
     int np, p0;
 };
 
-template <typename T>
-__device__ inline void shell_lane_load(const SysDev &S, const double *R, int s, ShellLane<T> &L) {
+__device__ inline void shell_lane_load(const SysDev &S, const double *R, int s, ShellLane &L) {
     const int a = S.basis.shell_atom[s];
     L.x = R[3 * a];
     L.y = R[3 * a + 1];
@@ -54,35 +51,30 @@ __device__ inline void shell_lane_load(const SysDev &S, const double *R, int s, 
     L.np = S.basis.shell_np[s];
     L.p0 = S.basis.shell_p0[s];
 #pragma unroll
-    for (int k = 0; k < ShellLane<T>::NP; ++k) {
+    for (int k = 0; k < ShellLane::NP; ++k) {
         const int p = L.p0 + max(min(k, L.np - 1), 0);
-        L.al[k] = (T)S.basis.prim_exp[p];
-        L.cp[k] = k < L.np ? (T)S.basis.prim_cp[p] : T(0);   // padded primitives carry cp = 0
-        L.alt[k] = (double)L.al[k] * 1.4426950408889634;
+        L.al[k] = S.basis.prim_exp[p];
+        L.cp[k] = k < L.np ? S.basis.prim_cp[p] : 0.0;   // padded primitives carry cp = 0
     }
 }
 
 // R0, u1, u2, u3 of ao_lane_radial for the lane's shell.
-template <typename T>
-__device__ inline void shell_lane_radial(const ShellLane<T> &L, const BasisDev &B, double rho, T *o) {
-    T r0 = T(0), r1 = T(0), r2 = T(0), r3 = T(0);
-    auto add = [&](T al, double alt, T cp) {
-        const T e = cp * prim_exp_neg<T>(al, alt, rho), al2 = al * al, al3 = al2 * al;
+__device__ inline void shell_lane_radial(const ShellLane &L, const BasisDev &B, double rho, double *o) {
+    double r0 = 0.0, r1 = 0.0, r2 = 0.0, r3 = 0.0;
+    auto add = [&](double al, double cp) {
+        const double e = cp * exp(-al * rho), al2 = al * al, al3 = al2 * al;
         r0 += e;
         r1 = fma(-al, e, r1);
         r2 = fma(al2, e, r2);
         r3 = fma(-al3, e, r3);
     };
 #pragma unroll
-    for (int k = 0; k < ShellLane<T>::NP; ++k) add(L.al[k], L.alt[k], L.cp[k]);
-    for (int k = ShellLane<T>::NP; k < L.np; ++k) {
-        const T al = (T)B.prim_exp[L.p0 + k];
-        add(al, (double)al * 1.4426950408889634, (T)B.prim_cp[L.p0 + k]);
-    }
+    for (int k = 0; k < ShellLane::NP; ++k) add(L.al[k], L.cp[k]);
+    for (int k = ShellLane::NP; k < L.np; ++k) add(B.prim_exp[L.p0 + k], B.prim_cp[L.p0 + k]);
     o[0] = r0;
-    o[1] = T(2) * r1;
-    o[2] = T(4) * r2;
-    o[3] = T(8) * r3;
+    o[1] = 2.0 * r1;
+    o[2] = 4.0 * r2;
+    o[3] = 8.0 * r3;
 }
 
 // The lane's monomial P = eta x^a y^b z^c at (x, y, z): its gradient, its
@@ -220,8 +212,8 @@ void k_adjoint_mfma(SysDev S, const T *__restrict__ C, const double *__restrict_
         // the sub-tile's shells, this lane's AO's among them
         const int s0 = ldc(S.basis.ao_shell + 16 * st), ns = ldc(S.basis.ao_shell + min(16 * st + 15, M - 1)) - s0 + 1;
         const int sj = shell - s0;
-        ShellLane<T> sl;
-        if (SHARED) shell_lane_load<T>(S, R, s0 + min(rj, ns - 1), sl);
+        ShellLane sl;
+        if constexpr (SHARED) shell_lane_load(S, R, s0 + min(rj, ns - 1), sl);
         T cB[KS];
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -251,16 +243,16 @@ void k_adjoint_mfma(SysDev S, const T *__restrict__ C, const double *__restrict_
 #pragma unroll 1
             for (int h = 0; h < 4; h += VU) {
                 V4 rs[VU];
-                if (SHARED) {
+                if constexpr (SHARED) {
                     // radial sums of the sub-tile's shells, XS at a time, at the
                     // turn's electrons, then to the lanes of their AOs
                     const int ec = min(16 * rt + MF::row(0, h) + re, N - 1);
                     const double px = sp[3 * ec], py = sp[3 * ec + 1], pz = sp[3 * ec + 2];
                     for (int q = 0; q < ns; q += XS) {
-                        if (ns > XS) shell_lane_load<T>(S, R, s0 + min(q + rj, ns - 1), sl);
+                        if (ns > XS) shell_lane_load(S, R, s0 + min(q + rj, ns - 1), sl);
                         const double dx = px - sl.x, dy = py - sl.y, dz = pz - sl.z;
-                        T o[4];
-                        shell_lane_radial<T>(sl, S.basis, dx * dx + dy * dy + dz * dz, o);
+                        double o[4];
+                        shell_lane_radial(sl, S.basis, dx * dx + dy * dy + dz * dz, o);
                         wave_sync_s();
                         if (rj < XS) xr[XS * ri + rj] = V4{o[0], o[1], o[2], o[3]};
                         wave_sync_s();
@@ -280,7 +272,7 @@ void k_adjoint_mfma(SysDev S, const T *__restrict__ C, const double *__restrict_
                     const double rho_d = dx * dx + dy * dy + dz * dz;
                     const T x = (T)dx, y = (T)dy, z = (T)dz, rho = (T)rho_d;
                     T R0, u1, u2, u3;
-                    if (SHARED) {
+                    if constexpr (SHARED) {
                         R0 = rs[v][0], u1 = rs[v][1], u2 = rs[v][2], u3 = rs[v][3];
                     } else {
                         ao_lane_radial<T, NPR>(al, S.basis, rho_d, R0, u1, u2, u3);

@@ -566,13 +566,9 @@ hipError_t launch_jas_values(int MJ, const Prepared &P, const double *pos, int64
     const dim3 g((unsigned)((rows + 63) / 64));
     // (wider tiles: half the barriers and row segments twice as long; the
     // FP64 tile of 32 functions would not fit the static LDS)
-    if constexpr (sizeof(T) == sizeof(float))
-        if (der) {
-            hipLaunchKernelGGL((k_jas_values<T, 5, 32>), g, dim3(256), 0, st, MJ, P.j32, pos, rows, out, der);
-            return hipGetLastError();
-        }
+    constexpr int MT = sizeof(T) == sizeof(float) ? 32 : 16;
     if (der)
-        hipLaunchKernelGGL((k_jas_values<T, 5, 16>), g, dim3(256), 0, st, MJ, P.j16, pos, rows, out, der);
+        hipLaunchKernelGGL((k_jas_values<T, 5, MT>), g, dim3(256), 0, st, MJ, MT == 32 ? P.j32 : P.j16, pos, rows, out, der);
     else
         hipLaunchKernelGGL((k_jas_values<T, 1, 16>), g, dim3(256), 0, st, MJ, P.j16, pos, rows, out, der);
     return hipGetLastError();
