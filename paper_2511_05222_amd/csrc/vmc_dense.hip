@@ -24,7 +24,7 @@
 //
 // Bound: the latency of a walker's chain of phases (barriers, loads of the MO
 // rows, FP64 products); issue takes 60 % at 37 orbitals, of that the matrix
-// cores 40 %.  Hence small blocks, as many on a CU as fit: from 48 orbitals on,
+// cores 40 %.  Hence small blocks, as many on a CU as fit: from 33 orbitals on,
 // after a sweep, one inverse at a time is held and loaded by the whole block,
 // three walkers a CU instead of two (32768 walkers of 47 orbitals FP32 3.39 ->
 // 2.76 ms, 16384 FP64 1.90 -> 1.61).  Blocks of six or eight wavefronts gained
@@ -69,8 +69,8 @@ __device__ inline double block_sum(double v, double *red) {
 }
 
 // STATE: the spin blocks' inverses come from the sweep (mb.kst) unless stale.
-// From 48 orbitals on only one is then held at a time, so that three blocks
-// (two of 64 orbitals) fit on a CU; otherwise wavefronts 0 and 1 load or form
+// From 33 orbitals on only one is then held at a time, so that three blocks
+// (two from 49 orbitals on) fit on a CU; otherwise wavefronts 0 and 1 load or form
 // both at the start.
 template <typename T, int KN, bool STATE>
 __global__ __launch_bounds__(64 * dense_waves(KN, STATE)) __attribute__((amdgpu_waves_per_eu(STATE && KN == 48 ? 3 : 2)))
@@ -91,7 +91,7 @@ void k_dense(SysDev S, const double *__restrict__ R, MeasBufs<T> mb, WalkerOut o
     int *perm = (int *)(smem + L.off_perm);      // [2][64]
     double *red = (double *)(smem + L.off_red);  // [24]
     double *Xs = (double *)(smem + L.off_x);     // [KN][ldk]     X, then T
-    double *Ks = (double *)(smem + L.off_k);     // [STATE ? 1 : 2][KN][ldk]  K[i][e]
+    double *Ks = (double *)(smem + L.off_k);     // [BOTH ? 2 : 1][KN][ldk]  K[i][e]
     const T *ph = mb.phi + (size_t)w * N * 5 * n;
     for (int i = tid; i < 3 * N; i += NT) p[i] = mb.pos[(size_t)w * N * 3 + i];
     __syncthreads();

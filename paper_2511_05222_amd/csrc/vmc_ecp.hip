@@ -574,7 +574,7 @@ __device__ inline void ao_lane_value_grad(const AoLane<T, NPR> &L, T x, T y, T z
 //   partials added in slot order.  Bound: issue; the staged y are padded with
 //   zeros to whole 16-byte vectors, so that the sums over orbitals need no
 //   branch and a quarter of the LDS reads, and the partials share their place
-//   (four blocks a CU; 13 orbitals, 16384 walkers FP32: 1.22 -> 1.03 ms).
+//   (four blocks a CU; 10 orbitals, 16384 walkers FP32: 1.22 -> 1.03 ms).
 // k_ecp_chain:
 //   phase 0 (threads over electrons): jo[e] = sum_{j != e} u'(r_ej) (r_e - r_j)/r_ej;
 //            (threads over pairs) es[e] = the sum of E_q = c'_q t_q over e's

@@ -186,8 +186,8 @@ __global__ __launch_bounds__(256) void k_jas_assemble(int N, int MJ, int64_t row
 // conflicts.  The xi1 column (AM 0, 1) is a dot product per row: lane
 // partial sums over its k, added over the four lanes of the row.  Bound: the
 // matrix cores and, AM 2, HBM (0.66 and 0.93 ms at their rates for 770000 rows
-// of 256); FP32 at three wavefronts a SIMD, a few registers spilled, 1.29, 1.11
-// and 1.25 ms for AM 1, 0, 2, at two 1.32, 1.23 and 1.33.
+// of 256); FP32 at three wavefronts a SIMD (24, 4 and 49 registers spilled) 1.29,
+// 1.11 and 1.25 ms for AM 1, 0, 2, at two 1.32, 1.23 and 1.33.
 template <typename T, int NTL, int AM, bool VA>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 1))) void k_jas_gemm(int MJ, int64_t rows, const T *__restrict__ A0,
                                                   const T *__restrict__ A1, const double *__restrict__ gb,

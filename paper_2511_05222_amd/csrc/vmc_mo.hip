@@ -152,8 +152,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(mo_waves<T,
 // Values only (the sweep's proposals and MO matrix), many rows: a wavefront
 // owns 64 rows, evaluates every shell of a tile at them (lane = row) into its
 // own part of LDS and multiplies all four row tiles itself, its entries of C
-// in registers, so no wavefront waits for another and the evaluation of one
-// overlaps the products of the others on its SIMD.
+// in registers, so no wavefront waits for another: while one waits for its loads
+// or LDS, the others of its SIMD evaluate or multiply.
 template <typename T, int NT>
 __global__ __launch_bounds__(256) void k_mo_values(int n, const T *__restrict__ Cp, ShellTiles tiles,
                                                    const double *__restrict__ pos, int64_t n_rows,
@@ -220,7 +220,7 @@ __global__ __launch_bounds__(256) void k_mo_values(int n, const T *__restrict__ 
 // kernel against k_mo_values: 131600 rows 72 / 85 us, 385024 rows 158 / 157 us;
 // 18 atoms, 606134 rows 184 / 190 us; 21 atoms, 6.2e6 rows 2.15 / 1.97 ms): its
 // blocks take four times the rows, so that fewer rows leave SIMDs without a
-// wavefront.  In FP64 the block kernel is faster at every size (six wavefronts
+// wavefront.  In FP64 the block kernel is faster at every size (five wavefronts
 // against two to a SIMD; 1.54e6 rows 1.11 / 1.19 ms).
 constexpr int64_t MO_VALUES_ROWS = 1 << 20;
 

@@ -46,9 +46,10 @@ constexpr int rebuild_ws_bytes() {
 template <typename T, int KN>
 __device__ inline void rebuild(const T *Aw, int n, int off, int nb, T (&Kr)[KN], int &sig, bool &bad, void *ws) {
     constexpr int RR = KN / 16, CC = KN / 4;
-    // Rows of A were written by this wavefront (and only by it): its loads go
-    // through the same L1, so a workgroup fence, which waits for the stores,
-    // is enough.  An agent fence writes back and invalidates the XCD's whole
+    // Rows of A were written by this wavefront (and only by it): its loads and
+    // stores go through the same L1 in their order, so it is enough that the
+    // compiler keeps that order, which a workgroup fence does (without an
+    // instruction here: workgroups are not split over CUs).  An agent fence writes back and invalidates the XCD's whole
     // L2 on every rebuild: 12.6 instead of 8.8 ms per 65536-walker FP32 launch
     // (21 atoms, average over the refresh period), 0.89 instead of 0.35 ms per
     // 16384-walker FP64 launch (9 atoms).
