@@ -63,12 +63,13 @@ PEAK_ALU = 78.6
 PEAK_HBM = 8000.0
 KERNELS = {"sweep": "k_sweep_r", "proposals": "k_mo_rows_mfma_proposals", "mo_rows": "k_mo_rows_mfma",
            "dense": "k_dense", "adjoint": "k_adjoint_mfma"}
-KERNEL_SRCS = {
-    "sweep": ("vmc_sweep.hip", "vmc_regs.hpp", "vmc_device.hpp", "vmc_pipeline.hpp"),
-    "proposals": ("vmc_sweep.hip", "vmc_mo.hip", "vmc_mfma.hpp", "vmc_device.hpp", "vmc_pipeline.hpp"),
-    "mo_rows": ("vmc_mo.hip", "vmc_mfma.hpp", "vmc_device.hpp", "vmc_pipeline.hpp"),
-    "dense": ("vmc_dense.hip", "vmc_mfma.hpp", "vmc_regs.hpp", "vmc_device.hpp", "vmc_pipeline.hpp"),
-    "adjoint": ("vmc_adjoint.hip", "vmc_mfma.hpp", "vmc_device.hpp", "vmc_pipeline.hpp"),
+_HEADERS = ("vmc_regs.hpp", "vmc_device.hpp", "vmc_kernels.hpp", "vmc_pipeline.hpp")
+KERNEL_SRCS = {   # (a kernel's own file and every header it is built from)
+    "sweep": ("vmc_sweep.hip", *_HEADERS),
+    "proposals": ("vmc_sweep.hip", "vmc_mo.hip", "vmc_mfma.hpp", *_HEADERS),
+    "mo_rows": ("vmc_mo.hip", "vmc_mfma.hpp", *_HEADERS),
+    "dense": ("vmc_dense.hip", "vmc_mfma.hpp", *_HEADERS),
+    "adjoint": ("vmc_adjoint.hip", "vmc_mfma.hpp", *_HEADERS),
 }
 COPY_BYTES = 1 << 30   # plain device copy used to calibrate the HBM byte counters
 WORKLOADS = {"9atom": 1, "21atom": 2}
