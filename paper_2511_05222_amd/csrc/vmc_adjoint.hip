@@ -16,10 +16,11 @@
 // of t_k and s_k go to tao; per electron the AO sums of t_k (dE_L/dr_e, the
 // determinant part) go to dedr_part, in a fixed order.
 //
-// Bound: issue (the matrix cores and the vector units of a SIMD take turns):
-// of the cycles of a row tile at 47 orbitals, FP32, 37 % are products and 44 %
-// the evaluations; FP64 34 % and 41 %, the rest latency that two wavefronts a
-// SIMD do not hide.
+// Bound: issue (the matrix cores and the vector units of a SIMD take turns): at
+// 47 orbitals, FP32, the matrix cores are busy 38 % of the cycles and 0.166
+// other vector instructions issue a cycle (at 2.6 cycles 43 %); FP64 34 % and
+// 0.100 (at 4.6 cycles 46 %), the rest latency that two wavefronts a SIMD do not
+// hide.
 //   FP64: an AO's lane used to form its shell's radial sums itself, each
 // shell's 2.3 times over with exponents read from memory; now four or eight
 // lanes a shell form them once (SHARED), in LDS until the AOs' lanes read them.

@@ -23,8 +23,9 @@
 // K, X and T stay FP64; K~ and Abar are stored in the arithmetic type T.
 //
 // Bound: the latency of a walker's chain of phases (barriers, loads of the MO
-// rows, FP64 products); issue takes 60 % at 37 orbitals, of that the matrix
-// cores 40 %.  Hence small blocks, as many on a CU as fit: from 33 orbitals on,
+// rows, FP64 products): at 37 orbitals the matrix cores are busy 27 % of the
+// cycles and 0.11 other vector instructions issue a cycle (2.6 cycles each as
+// integer, 4.6 as FP64 ones).  Hence small blocks, as many on a CU as fit: from 33 orbitals on,
 // after a sweep, one inverse at a time is held and loaded by the whole block,
 // three walkers a CU instead of two (32768 walkers of 47 orbitals FP32 3.39 ->
 // 2.76 ms, 16384 FP64 1.90 -> 1.61).  Blocks of six or eight wavefronts gained

@@ -53,8 +53,9 @@ __device__ inline unsigned wave_max_u32(unsigned v) {
 // registers q = 0 of group k % 4.  The column goes through LDS to the other
 // groups (which hold the same rows), the pivot row's entries to the lanes of
 // their own group (which hold the same columns); every lane then updates its
-// KN^2 / 64 entries.  Bound: VALU issue, about 310 cycles a step at KN = 48, of
-// which the 36 FMAs take 166.  (A lane to each row, the pivot row broadcast by
+// KN^2 / 64 entries.  Bound: the latency of a step's chain (two LDS round trips,
+// a maximum, a reciprocal): about 600 of a SIMD's cycles a step at KN = 48 with
+// three wavefronts, of which 310 issue, 166 of them the 36 FMAs.  (A lane to each row, the pivot row broadcast by
 // two lane reads per entry, issues 3 instructions for each of KN entries a step
 // instead of 1 for KN^2 / 64, on KN of the 64 lanes.  A rebuild of all walkers
 // within the FP32 sweep of 65536 walkers, 21 atoms: 1.47 -> 0.77 ms; within the
