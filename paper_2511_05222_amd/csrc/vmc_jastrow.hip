@@ -437,10 +437,10 @@ __device__ inline JasTerm<T> jas_term(const BasisDev &JB, const JasFn<T> &fn, co
 // mu = lane + 64 k; per electron the sum over functions by a wavefront sum,
 // per function the wavefronts' partial sums added in wavefront order.  The
 // terms and the sums inside a wavefront are in the arithmetic type, FP64 from
-// the wavefront sums on.  Bound: issue (0.25 vector
-// instructions a cycle at 2.6 cycles each), since a lane's functions and the next
-// electron's values are held ahead of their use, at three wavefronts a SIMD (256 functions, 94
-// electrons, 8192 walkers FP32: 1.87 -> 1.11 ms).
+// the wavefront sums on.  Bound: issue (0.25 vector instructions a cycle at 2.6
+// cycles each), since a lane's functions and the next electron's values are held
+// ahead of their use, at three wavefronts a SIMD (256 functions, 94 electrons,
+// 8192 walkers FP32: 1.87 -> 1.11 ms).
 template <typename T>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 1))) void k_jas_adjoint(BasisDev JB, const double *__restrict__ R, int A, int N, int MJ,
                                                      int64_t rows, int64_t row0, const double *__restrict__ pos,
